@@ -199,17 +199,19 @@ __global__ __launch_bounds__(kThreads) void k_row(XArgs a) {
       const int who = (int)__builtin_ctzll(todo);
       const int sx = (int)readlane((uint32_t)x, who), sl = (int)readlane((uint32_t)lo, who), sh = (int)readlane((uint32_t)hi, who);
       uint32_t bd = 0xFFFFFFFFu;
-      int bc = sl;
-      for (int c0 = sl; c0 <= sh; c0 += kWave) {  // ascending: the smallest column of a tie comes first
-        const int c = c0 + lane();
-        const uint32_t d = c <= sh ? dist(g, sx, c) : 0xFFFFFFFFu;
-        const uint32_t m = wave_min(d);
-        if (m < bd) {
-          bd = m;
-          bc = c0 + (int)__builtin_ctzll(ballot(d == m));
+      uint32_t bc = 0xFFFFFFFFu;
+#pragma unroll 4
+      for (int c = sl + lane(); c <= sh; c += kWave) {
+        const uint32_t d = dist(g, sx, c);
+        if (d < bd) {
+          bd = d;
+          bc = (uint32_t)c;
         }
       }
-      if (lane() == who) best = bc;
+      const uint32_t m = wave_min(bd);
+      const int at = sh - sl < kWave ? sl + (int)__builtin_ctzll(ballot(bd == m))
+                                     : (int)wave_min(bd == m ? bc : 0xFFFFFFFFu);
+      if (lane() == who) best = at;
     }
     return best;
   };
@@ -250,8 +252,9 @@ __global__ __launch_bounds__(kThreads) void k_row(XArgs a) {
   }
   for (; s > 1; s >>= 1) {
     const int n = W > s ? (W - 1 - s) / (2 * s) + 1 : 0;  // odd multiples of s below W
-    for (int i0 = w0; i0 < n; i0 += kThreads) {
-      const int i = i0 + lane(), x = s * (2 * i + 1);
+    for (int i0 = 0; i0 < n; i0 += kThreads) {
+      // dealt to the waves in turn: the few anchors of the first levels have long ranges
+      const int i = i0 + lane() * (kThreads / kWave) + w0 / kWave, x = s * (2 * i + 1);
       const bool on = i < n;
       const int lo = on ? arg[(x - s) >> 1] : 0, hi = on && x + s < W ? arg[(x + s) >> 1] : W - 1;
       const int best = search(on, x, lo, hi);
@@ -311,10 +314,10 @@ extern "C" int32_t iwpp_edt_exact(iwpp_ctx* ctx, const uint8_t* binary, int32_t*
   a.nseg = nseg;
   hipStream_t st = static_cast<hipStream_t>(stream);
   // Rows wider than 8192 take 1024 threads: their 3 bytes of LDS a column leave
-  // room for few workgroups per CU.
-  const bool wide = width > 8192;
+  // room for few workgroups per CU.  Rows up to 512 take one wave each.
+  const int threads = width > 8192 ? 1024 : (width > 512 ? 256 : 64);
   const uint32_t lds = 2u * ((uint32_t)width + ((uint32_t)width + 1u) / 2u);
-  void (*row)(xedt::XArgs) = wide ? &xedt::k_row<1024> : &xedt::k_row<256>;
+  void (*row)(xedt::XArgs) = threads == 1024 ? &xedt::k_row<1024> : (threads == 256 ? &xedt::k_row<256> : &xedt::k_row<64>);
   if (lds > 64u * 1024u && hipFuncSetAttribute(reinterpret_cast<const void*>(row), hipFuncAttributeMaxDynamicSharedMemorySize,
                                                (int)lds) != hipSuccess) {
     (void)hipGetLastError();
@@ -323,7 +326,7 @@ extern "C" int32_t iwpp_edt_exact(iwpp_ctx* ctx, const uint8_t* binary, int32_t*
   ctx->rec.begin(IWPP_K_XEDT, st);
   hipLaunchKernelGGL(xedt::k_mask, dim3((unsigned)((width + 63) / 64), (unsigned)nsuper), dim3(64 * xedt::kSuper), 0, st, a);
   hipLaunchKernelGGL(xedt::k_col, dim3((unsigned)((width + 255) / 256), (unsigned)nseg), dim3(256), 0, st, a);
-  hipLaunchKernelGGL(row, dim3((unsigned)height), dim3(wide ? 1024 : 256), lds, st, a);
+  hipLaunchKernelGGL(row, dim3((unsigned)height), dim3(threads), lds, st, a);
   ctx->rec.end(st);
   if (hipGetLastError() != hipSuccess) return fail(ctx, IWPP_EDEVICE, "edt_exact: launch failed");
   ctx->last_stream = st;
