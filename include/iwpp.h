@@ -78,7 +78,8 @@ typedef struct {
    * 8-connectivity, 2 with 4-connectivity). */
   int32_t mr_seed_sweeps;
   /* Waves per workgroup of the persistent kernels, 4 or 8 (0 = 4): the
-   * workgroup size (the paper's threads per block; a wave holds one tile). */
+   * workgroup size (the paper's threads per block; a reconstruction tile is
+   * one wave's, a distance transform tile one workgroup's). */
   int32_t wg_waves;
   /* Work-list items a wave stages in LDS before one global atomic appends
    * them (the depth of the paper's per-block queue): 1 .. 64 (0 = 64). */

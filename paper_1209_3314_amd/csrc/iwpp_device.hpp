@@ -56,6 +56,14 @@ __device__ __forceinline__ T atomic_max(T* p, T v) {
 
 // ---- wave helpers -------------------------------------------------------------
 __device__ __forceinline__ int lane() { return (int)__lane_id(); }
+// A per-lane value the compiler knows nothing about: what is computed from it
+// is computed where it is used.  In a persistent kernel it would otherwise be
+// moved out of all loops, kept in registers over the whole kernel and, past
+// their number, in scratch memory, whose reloads wait behind a visit's stores.
+__device__ __forceinline__ int local_copy(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 __device__ __forceinline__ int mbcnt(uint64_t m) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));

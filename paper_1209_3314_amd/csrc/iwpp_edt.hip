@@ -13,10 +13,11 @@
 // not depend on thread order.
 //
 // How: K rounds per tile visit (temporal blocking).  The image is cut into
-// 26x26 tiles.  A visit loads a tile with a K-pixel halo (a 34x34 region) from
-// the state after round r into LDS and applies the operator K times, each time
-// on a region one pixel smaller on every side, which leaves the tile exactly
-// at round r + K; the tile goes to the other state buffer.  One step of the
+// tiles of TE x TE pixels, TE = 64 - 2K.  A workgroup visits a tile: it loads
+// the tile with a K-pixel halo (a 64 x 64 region) from the state after round r
+// into LDS and runs K rounds there.  Round i leaves the pixels at least i away
+// from the region's edge as the operator would, so after K rounds the tile is
+// exactly at round r + K and goes to the other state buffer.  One step of the
 // persistent kernel visits the listed tiles and ends in one grid barrier, so
 // K rounds cost one barrier.  Which tiles a step must visit follows from two
 // facts: a pixel's value only improves (its own previous feature is always a
@@ -28,17 +29,32 @@
 // the other buffer: a tile that is not visited holds equal values in both
 // buffers, and every pixel a visit reads is at round r.
 //
-// The tiles of a step are a work list split into eight sub-lists, one per
-// group of workgroups (one per XCD), appended to with one atomic per wave
-// flush and consumed evenly by all waves in the next step; a per-tile flag
-// keeps a tile on a step's list once.
+// A round in LDS is a push.  Only a pixel that changed in the previous round
+// can improve a neighbour (the others' offers were weighed before), so the
+// pixels of the previous round's change masks are gathered into a list and
+// offer their feature to each neighbour: the offered (squared distance,
+// feature) is one 64-bit key, compared with the neighbour's key and, where
+// smaller, taken with an LDS 64-bit minimum.  Every lane holds its sources'
+// features in registers before the first offer of a round, so a pixel offers
+// what it held at the end of the previous round whatever the order; the
+// minimum does not depend on the order either.
 //
-// State is the feature's packed coordinates (y << 16 | x), 4 bytes per pixel.
-// A candidate's squared distance is one saturating packed 16-bit subtraction
-// and one 2-term dot product; "none" is the packed pair (-32768, -32768),
-// whose saturated distance exceeds that of any real feature (coordinates are
-// below 32767), and whose packed value exceeds any real feature's, so the
-// lexicographic minimum needs no special case for it.
+// Bound: 9 bytes a pixel have to move (30 us for 4096^2 at the copy rate); the
+// time goes to a visit's serial chain -- in cycles 5 k to load, per round 1.4 k
+// to list the sources and 0.9 k to push them, 5 k to store and list tiles --
+// which four workgroups per CU (40 KB of keys each) hide in part, and to the
+// slowest visit of each step.  Measured (30% features, rounds kernel): 4096^2
+// 1124 us, 389 x 517 310 us.  Before, a pull over the neighbourhood of every
+// change (26 x 26 tiles, four rounds a visit, one wave each; eleven
+// evaluations of nine candidates per changed pixel): 1312 and 505 us.
+//
+// The tiles of a step are a work list split into eight sub-lists, one per
+// group of workgroups (one per XCD), appended to with one atomic per flush and
+// consumed evenly by all workgroups in the next step; a per-tile flag keeps a
+// tile on a step's list once.
+//
+// State in memory is the feature's packed coordinates (y << 16 | x), 4 bytes
+// per pixel.
 #include "iwpp_device.hpp"
 #include "iwpp_internal.hpp"
 
@@ -47,17 +63,18 @@ namespace edt {
 
 constexpr int K = kEdtHalo;        // rounds per step = halo width
 constexpr int TE = kEdtTile;       // tile side
-constexpr int RP = TE + 2 * K;     // region side
-constexpr int kCPR = (RP + 3) / 4; // 16-byte chunks per region row
-constexpr int PE = 4 * kCPR;       // LDS row pitch (words)
-constexpr int kWavesPerBlock = 4;  // the initialisation kernel
-constexpr int kStageCap = 64;       // LDS work-list stage per wave (iwpp_options.stage_depth caps it)
+constexpr int R = TE + 2 * K;      // region side: one 64-bit mask word per row
+constexpr int P = R + 2;           // LDS pitch: the region has a ring of pixels that never change around it
+constexpr int kStageCap = 64;      // LDS work-list stage (iwpp_options.stage_depth caps it)
+constexpr int kPart = 256;         // sources a wave lists at a time
 constexpr uint32_t kMaxSteps = (1u << 20) / K;
-static_assert(RP - 2 <= 32, "a round's region row must fit 32 lanes");
-static_assert(K % 4 == 0, "region chunks must not straddle the image's left edge");
+static_assert(R == 64, "one mask bit per region column, one lane per region row");
+static_assert(K % 4 == 0 && TE % 4 == 0, "16-byte chunks must not straddle the image's left edge or a tile's");
 static_assert(K <= TE, "a change must reach no farther than the neighbouring tiles");
+static_assert(TE == kEdtTile && TE <= 64, "change records are one 64-bit word per tile row");
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef int v4i __attribute__((ext_vector_type(4)));
 typedef short s2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u2 __attribute__((ext_vector_type(2)));
 
@@ -70,7 +87,8 @@ __device__ __forceinline__ uint32_t umin32(uint32_t a, uint32_t b) { return a < 
 // Narrow (sides up to 32767): coordinates are signed 16-bit fields and "none"
 // is (-32768, -32768).  A squared distance is one saturating packed 16-bit
 // subtraction and one 2-term dot product; none's saturated distance,
-// 2 * 32767^2, exceeds that of any real feature, so it needs no special case.
+// 2 * 32767^2, exceeds that of any real feature (coordinates are below 32767),
+// and its packed value any real feature's, so it needs no special case.
 //
 // Wide (sides up to 46340, with (h-1)^2 + (w-1)^2 < 2^31 so that squared
 // distances fit the int32 output): coordinates are unsigned 16-bit fields and
@@ -92,52 +110,32 @@ struct Coord<false> {
     asm("v_dot2_i32_i16 %0, %1, %1, 0" : "=v"(r) : "v"(__builtin_bit_cast(uint32_t, e)));
     return r;
   }
-  // The lexicographically smallest (squared distance to q, feature) of the N
-  // candidate features f[]: the smallest distance dm first, then the smallest
-  // feature among the candidates at distance dm.  Distances are below 2^31,
-  // so dm - d has its sign bit set exactly when d > dm; OR-ing that bit into
-  // the feature puts every candidate farther than dm above every real feature
-  // (real features are below 2^31; none has the bit already and is farthest
-  // of all), and one more minimum picks the answer: 32-bit minima only, no
-  // 64-bit key comparisons.
-  template <int N>
-  __device__ static __forceinline__ uint32_t nearest(uint32_t q, const uint32_t (&f)[N]) {
-    uint32_t d[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) d[i] = d2(q, f[i]);
-    uint32_t dm = d[0];
-#pragma unroll
-    for (int i = 1; i < N; ++i) dm = umin32(dm, d[i]);
-    uint32_t fm = 0xFFFFFFFFu;
-#pragma unroll
-    for (int i = 0; i < N; ++i) fm = umin32(fm, f[i] | ((dm - d[i]) & 0x80000000u));
-    return fm;
+  // What the distances from q's neighbours to the real feature f are computed from.
+  __device__ static __forceinline__ uint32_t base(uint32_t q, uint32_t f) {
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(s2, q) - __builtin_bit_cast(s2, f));
+  }
+  __device__ static __forceinline__ uint32_t d2_at(uint32_t b, uint32_t, uint32_t step) {
+    const s2 e = __builtin_bit_cast(s2, b) + __builtin_bit_cast(s2, step);
+    uint32_t r;
+    asm("v_dot2_i32_i16 %0, %1, %1, 0" : "=v"(r) : "v"(__builtin_bit_cast(uint32_t, e)));
+    return r;
   }
 };
 
 template <>
 struct Coord<true> {
   static constexpr uint32_t none = 0xFFFFFFFFu;
-  __device__ static __forceinline__ uint32_t d2(uint32_t q, uint32_t f) {
+  __device__ static __forceinline__ uint32_t real_d2(uint32_t q, uint32_t f) {
     const u2 a = __builtin_bit_cast(u2, q), b = __builtin_bit_cast(u2, f);
     const u2 e = __builtin_elementwise_max(a, b) - __builtin_elementwise_min(a, b);
-    const uint32_t r = __builtin_amdgcn_udot2(e, e, 0u, false);
-    return f == none ? 0xFFFFFFFFu : r;
+    return __builtin_amdgcn_udot2(e, e, 0u, false);
   }
-  // Lexicographic minimum: the smallest distance, then the smallest feature
-  // among the candidates at that distance (packed (y, x) order is index order).
-  template <int N>
-  __device__ static __forceinline__ uint32_t nearest(uint32_t q, const uint32_t (&f)[N]) {
-    uint32_t d[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) d[i] = d2(q, f[i]);
-    uint32_t dm = d[0];
-#pragma unroll
-    for (int i = 1; i < N; ++i) dm = umin32(dm, d[i]);
-    uint32_t fm = 0xFFFFFFFFu;
-#pragma unroll
-    for (int i = 0; i < N; ++i) fm = umin32(fm, d[i] == dm ? f[i] : 0xFFFFFFFFu);
-    return fm;
+  __device__ static __forceinline__ uint32_t d2(uint32_t q, uint32_t f) {
+    return f == none ? 0xFFFFFFFFu : real_d2(q, f);
+  }
+  __device__ static __forceinline__ uint32_t base(uint32_t q, uint32_t) { return q; }
+  __device__ static __forceinline__ uint32_t d2_at(uint32_t b, uint32_t f, uint32_t step) {
+    return real_d2(__builtin_bit_cast(uint32_t, __builtin_bit_cast(u2, b) + __builtin_bit_cast(u2, step)), f);
   }
 };
 
@@ -168,209 +166,214 @@ constexpr uint32_t kOutside = 0xFFFFFFF0u;
 constexpr uint32_t kStatePad = 16u;  // readable bytes after the last pixel of a state buffer
 static_assert(kStatePad <= kEdtStatePad, "state buffers must be padded");
 
-// Per-wave LDS: the region, the change masks of two consecutive rounds (one
-// bit per region pixel, a 64-bit word per row) and the active-pixel list.
-constexpr int kMaxActive = (RP - 2) * (RP - 2);  // pixels of round 1
-constexpr int kPerLane = (kMaxActive + kWave - 1) / kWave;
-struct WaveLds {
-  uint32_t F[RP * PE];
-  unsigned long long chg[2][RP];
-  uint16_t list[kMaxActive];
+// LDS of a workgroup.  key: (squared distance << 32 | feature) of every region
+// pixel and the ring around it; pixels outside the image and the ring hold 0,
+// which no offer is below, so they never change and need no bounds checks.
+// chg: the pixels that changed in a round (bit = region column), for two
+// consecutive rounds.  list: a wave's sources (region row << 6 | column).
+// any[i & 1]: round i has a source.
+template <int WPB>
+struct WgLds {
+  unsigned long long key[P * P];
+  unsigned long long chg[2][R];
+  uint16_t list[WPB][kPart];
+  uint32_t any[2];
 };
 
+__device__ __forceinline__ int at(int row, int col) { return (row + 1) * P + col + 1; }
+
 // Load the region of tile tr (rows and columns from K before the tile) from
-// `src` into S; pixels outside the image read as none.  kCPR 16-byte chunks
-// per row, all issued with no branch in between so the wave waits for memory
-// once; a chunk cut by the image's right edge is loaded whole (the state
-// buffers are padded) and its outside words replaced.
-template <bool kWide>
-__device__ void load_region(const uint32_t* src, const TileRef& tr, uint32_t* S) {
-  constexpr uint32_t kNone = Coord<kWide>::none;
+// `src` into the keys: 16-byte chunks, all loads issued before the first is
+// used; a chunk cut by the image's right edge is loaded whole (the state
+// buffers are padded).
+template <bool kWide, int WPB>
+__device__ __forceinline__ void load_region(const uint32_t* src, const TileRef& tr, WgLds<WPB>& L) {
   const EdtJob& j = tr.j;
   const int ry0 = tr.ty * TE - K, rx0 = tr.tx * TE - K;
   const int row0 = ry0 > 0 ? ry0 : 0;
-  const int row1 = ry0 + RP < j.h ? ry0 + RP : j.h;
+  const int row1 = ry0 + R < j.h ? ry0 + R : j.h;
   const __amdgpu_buffer_rsrc_t rs = rows_rsrc(src, j, row0, row1 - row0, kStatePad);
-  constexpr int kChunks = RP * kCPR;
-  constexpr int kPer = (kChunks + kWave - 1) / kWave;
+  constexpr int kPer = R * R / 4 / (kWave * WPB);
+  const int t = local_copy((int)threadIdx.x), c = 4 * (t & 15), xs = rx0 + c;
   v4u v[kPer];
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int idx = lane() + k * kWave;
-    const int ry = idx / kCPR, c = idx - ry * kCPR;
-    const int y = ry0 + ry, xs = rx0 + 4 * c;
-    const bool ok = idx < kChunks && y >= 0 && y < j.h && xs >= 0 && xs < j.w;
+    const int y = ry0 + (t >> 4) + k * (4 * WPB);
+    const bool ok = y >= 0 && y < j.h && xs >= 0 && xs < j.w;
     const uint32_t off = ok ? ((uint32_t)(y - row0) * (uint32_t)j.w + (uint32_t)xs) * 4u : kOutside;
     v[k] = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kSc1));
   }
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int idx = lane() + k * kWave;
-    const int ry = idx / kCPR, c = idx - ry * kCPR;
-    const int y = ry0 + ry, xs = rx0 + 4 * c;
+    const int row = (t >> 4) + k * (4 * WPB), y = ry0 + row;
     const bool row_ok = y >= 0 && y < j.h;
-    v4u o;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) o[b] = (row_ok && xs + b >= 0 && xs + b < j.w) ? v[k][b] : kNone;
-    if (idx < kChunks) *reinterpret_cast<v4u*>(&S[ry * PE + 4 * c]) = o;
+    for (int b = 0; b < 4; ++b) {
+      const int x = xs + b;
+      const uint32_t f = v[k][b], d = Coord<kWide>::d2(pack_yx(y, x), f);
+      const bool ok = row_ok && x >= 0 && x < j.w;
+      L.key[at(row, c + b)] = ok ? ((unsigned long long)d << 32 | f) : 0ull;
+    }
   }
-  wave_sync();
 }
 
-// Zone bits of a tile pixel (cy, cx): which neighbouring tiles lie within K
-// pixels of it -- 1 top, 2 bottom, 3 left, 4 right, 5 top-left, 6 top-right,
-// 7 bottom-left, 8 bottom-right (bit 0, the tile itself, is set by callers).
-__device__ __forceinline__ uint32_t zone_bits(int cy, int cx) {
-  const bool t = cy < K, b = cy >= TE - K, l = cx < K, r = cx >= TE - K;
-  return (t ? 2u : 0u) | (b ? 4u : 0u) | (l ? 8u : 0u) | (r ? 16u : 0u) | (t && l ? 32u : 0u) |
+// Which neighbouring tiles lie within K pixels of the marked pixels of a tile
+// row (`m`, bit = tile column) -- 1 top, 2 bottom, 3 left, 4 right, 5
+// top-left, 6 top-right, 7 bottom-left, 8 bottom-right -- and bit 0, the tile
+// itself, if any is marked.
+__device__ __forceinline__ uint32_t zone_bits(unsigned long long m, int row) {
+  const bool any = m != 0ull, t = any && row < K, b = any && row >= TE - K;
+  const bool l = (m & ((1ull << K) - 1ull)) != 0ull, r = (m >> (TE - K)) != 0ull;
+  return (any ? 1u : 0u) | (t ? 2u : 0u) | (b ? 4u : 0u) | (l ? 8u : 0u) | (r ? 16u : 0u) | (t && l ? 32u : 0u) |
          (t && r ? 64u : 0u) | (b && l ? 128u : 0u) | (b && r ? 256u : 0u);
 }
 
-// K rounds of the operator on the region in LDS, in place.  Round i
-// computes region rows and columns [i, RP-i) from round i-1's values, only at
-// the pixels with a neighbour (or themselves) changed in round i-1 -- the
-// others cannot change -- gathered into a list from the previous round's
-// change masks; for round 1 those are the previous step's last-round changes
-// over the region (`prev_step_issue` / `prev_step_finish`; for the first
-// step, the contour features recorded by `k_init`).  Pixels outside the image
-// never enter the list (they stay none).  Each lane computes up to kPerLane
-// list pixels, kBatch at a time with their loads issued together, into
-// registers, and writes the changed ones after the whole wave has read, so
-// every read sees round i-1.  Accumulates the changed tile pixels (over the
-// rounds), the zone mask (bit 0: a tile pixel changed; bits 1..8: a change in
-// round K within K pixels of that side) and the last round (1..K) with a
-// change.
-constexpr int kBatch = 2;
-static_assert(kPerLane % kBatch == 0, "whole batches");
-template <int CONN, bool kWide>
-__device__ void relax_steps(WaveLds& L, const TileRef& tr, uint32_t& changed, uint32_t& zone, uint32_t& last) {
-  static_assert(RP <= 64, "one mask bit per region column");
-  constexpr int NC = CONN == 8 ? 9 : 5;
-  const EdtJob& j = tr.j;
-  const int ry0 = tr.ty * TE - K, rx0 = tr.tx * TE - K;
-  const int l = lane();
-  // Region columns and this lane's region row that lie inside the image.
-  const int c_lo = rx0 < 0 ? -rx0 : 0, c_hi = j.w - rx0 < RP ? j.w - rx0 : RP;
-  const unsigned long long in_cols = ((c_hi >= 64 ? ~0ull : ((1ull << c_hi) - 1ull))) & ~((1ull << c_lo) - 1ull);
-  const bool in_row = ry0 + l >= 0 && ry0 + l < j.h;
+// The lanes' zone bits OR-ed over the wave.
+__device__ __forceinline__ uint32_t any_zone(uint32_t zone) {
+  uint32_t z = 0;
+#pragma unroll
+  for (int b = 0; b < 9; ++b)
+    if (ballot((zone >> b) & 1u)) z |= 1u << b;
+  return z;
+}
+
+constexpr unsigned long long kTileCols = ((1ull << TE) - 1ull) << K;  // region columns of the tile
+
+// The offers of one source (region row << 6 | column, feature f) to its
+// neighbours: taken where smaller than the neighbour's key, which marks the
+// neighbour as changed in this round.
+template <int CONN, bool kWide, int WPB>
+__device__ __forceinline__ void push(WgLds<WPB>& L, unsigned long long* now, uint32_t e, uint32_t f, uint32_t q0) {
+  constexpr int NC = CONN == 8 ? 8 : 4;
+  constexpr int kDy[8] = {-1, 1, 0, 0, -1, -1, 1, 1}, kDx[8] = {0, 0, -1, 1, -1, 1, -1, 1};
+  const int row = (int)(e >> 6), col = (int)(e & 63u);
+  unsigned long long* k = &L.key[at(row, col)];
+  const uint32_t q = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u2, q0) + __builtin_bit_cast(u2, pack_yx(row, col)));
+  const uint32_t b = Coord<kWide>::base(q, f);
+  uint32_t took[3] = {0u, 0u, 0u};  // by row: bit 0 left, 1 same column, 2 right
+#pragma unroll
+  for (int n = 0; n < NC; ++n) {
+    const uint32_t step = ((uint32_t)kDy[n] << 16) | ((uint32_t)kDx[n] & 0xffffu);
+    const unsigned long long key = (unsigned long long)Coord<kWide>::d2_at(b, f, step) << 32 | f;
+    const unsigned long long old =
+        __hip_atomic_fetch_min(&k[kDy[n] * P + kDx[n]], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    took[kDy[n] + 1] |= (old > key ? 1u : 0u) << (kDx[n] + 1);
+  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+    if (took[d])  // never beyond the region: the ring takes nothing
+      __hip_atomic_fetch_or(&now[row + d - 1], col > 0 ? (unsigned long long)took[d] << (col - 1) : (unsigned long long)took[d] >> 1,
+                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// K rounds on the region in LDS.  Round i's sources are the pixels that
+// changed in round i-1 (for round 1, chg[0]: the last round of the previous
+// step, or the contour features of the image) at least i-1 away from the
+// region's edge; a round without any ends the visit's work.  Each wave takes
+// every WPB-th row, a lane every WPB-th pixel of a row, so that a long run of
+// changes is walked by several lanes.  Per lane: the tile's pixels that
+// changed (over the rounds) and the last round that changed one.
+template <int CONN, bool kWide, int WPB>
+__device__ __forceinline__ void relax_steps(WgLds<WPB>& L, const TileRef& tr, uint32_t& changed, uint32_t& last) {
+  constexpr int kParts = (64 / WPB) * 64 / kPart, kPer = kPart / kWave;
+  const int l = local_copy(lane()), w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int row = (l / WPB) * WPB + w;
+  const uint32_t half = (WPB == 4 ? 0x11111111u : 0x01010101u) << (l % WPB);
+  const unsigned long long mine = (unsigned long long)half << 32 | half;  // this lane's columns
+  const unsigned long long own = row >= K && row < K + TE ? kTileCols : 0ull;
+  const uint32_t q0 = pack_yx(tr.ty * TE - K, 0) | ((uint32_t)(tr.tx * TE - K) & 0xffffu);
+  uint16_t* list = L.list[w];
 #pragma unroll 1
   for (int i = 1; i <= K; ++i) {
     unsigned long long* now = L.chg[i & 1];
-    const unsigned long long* prev = L.chg[(i - 1) & 1];
-    // The active list of round i (for round 1, chg[0] holds the previous
-    // step's last-round changes over the region).
-    uint32_t n;
-    {
-      const unsigned long long win = ((1ull << (RP - i)) - 1ull) & ~((1ull << i) - 1ull) & in_cols;  // columns [i, RP-i)
-      unsigned long long m = 0;
-      if (l >= i && l < RP - i && in_row) {
-        m = prev[l - 1] | prev[l] | prev[l + 1];
-        m = (m | (m << 1) | (m >> 1)) & win;
-      }
-      // exclusive prefix of the per-row counts over the lanes
-      const uint32_t c = (uint32_t)__popcll(m);
-      const uint32_t incl = wave_incl_sum(c);
-      n = (uint32_t)readlane(incl, kWave - 1);
-      uint32_t at = incl - c;
-      while (m) {
-        const int col = __ffsll((long long)m) - 1;
-        m &= m - 1;
-        L.list[at++] = (uint16_t)((l << 8) | col);
-      }
+    const unsigned long long all = L.chg[(i - 1) & 1][row] & mine;
+    if (l % WPB == 0) now[row] = 0ull;
+    if (i > 1) {
+      const uint32_t c = (uint32_t)__popcll(all & own);
+      changed += c;
+      if (c) last = (uint32_t)(i - 1);
     }
-    if (l < RP) now[l] = 0ull;
-    wave_sync();
-    // Compute (reads only): batches of kBatch list pixels per lane.
-    uint32_t res[kPerLane];
-    uint32_t chg = 0;  // bit k: list pixel k of this lane changed
+    const unsigned long long m = row >= i - 1 && row <= R - i ? all & (~0ull << (i - 1)) & (~0ull >> (i - 1)) : 0ull;
+    uint32_t lo = (uint32_t)m, hi = (uint32_t)(m >> 32);
+    const uint32_t c = (uint32_t)(__popc(lo) + __popc(hi)), incl = wave_incl_sum(c), n = readlane(incl, kWave - 1);
+    if (n != 0u && l == 0) L.any[i & 1] = 1u;
+    if (threadIdx.x == 0) L.any[(i + 1) & 1] = 0u;  // last read in round i-1, next set in round i+1
+    uint32_t a = incl - c, b = a + (uint32_t)__popc(lo);
+    const uint32_t r = (uint32_t)row << 6;
+    uint32_t ent[kParts * kPer], f[kParts * kPer];
 #pragma unroll
-    for (int k0 = 0; k0 < kPerLane; k0 += kBatch) {
-      if ((uint32_t)(k0 * kWave) < n) {  // wave-uniform
-        uint32_t f[kBatch][NC], ent[kBatch];
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-          const uint32_t idx = (uint32_t)((k0 + b) * kWave + l);
-          // past the list: a harmless in-region pixel (row 1, column 1); its result is not used
-          ent[b] = idx < n ? (uint32_t)L.list[idx] : 0x101u;
+    for (int p = 0; p < kParts; ++p) {
+      if (p > 0 && __builtin_expect(n <= (uint32_t)(p * kPart), 1)) break;  // wave-uniform
+      uint32_t x = lo, y = hi, ax = a - (uint32_t)(p * kPart), bx = b - (uint32_t)(p * kPart);
+      while (x | y) {  // both halves of the row at once
+        if (x) {
+          if (ax < (uint32_t)kPart) list[ax] = (uint16_t)(r | (uint32_t)__builtin_ctz(x));
+          x &= x - 1u;
+          ++ax;
         }
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-          const uint32_t* c = &L.F[(int)(ent[b] >> 8) * PE + (int)(ent[b] & 0xffu)];
-          f[b][0] = c[0];
-          f[b][1] = c[-PE];
-          f[b][2] = c[PE];
-          f[b][3] = c[-1];
-          f[b][4] = c[1];
-          if (CONN == 8) {
-            f[b][5] = c[-PE - 1];
-            f[b][6] = c[-PE + 1];
-            f[b][7] = c[PE - 1];
-            f[b][8] = c[PE + 1];
-          }
-        }
-#pragma unroll
-        for (int b = 0; b < kBatch; ++b) {
-          const uint32_t q = pack_yx(ry0 + (int)(ent[b] >> 8), rx0 + (int)(ent[b] & 0xffu));
-          res[k0 + b] = Coord<kWide>::nearest(q, f[b]);
-          const uint32_t idx = (uint32_t)((k0 + b) * kWave + l);
-          chg |= (idx < n && res[k0 + b] != f[b][0]) ? (1u << (k0 + b)) : 0u;
+        if (y) {
+          if (bx < (uint32_t)kPart) list[bx] = (uint16_t)(r | 32u | (uint32_t)__builtin_ctz(y));
+          y &= y - 1u;
+          ++bx;
         }
       }
-    }
-    wave_sync();
-    // Write back the changed pixels, recording them.
+      wave_sync();
 #pragma unroll
-    for (int k = 0; k < kPerLane; ++k) {
-      if (!((chg >> k) & 1u)) continue;
-      const uint32_t e = L.list[(uint32_t)(k * kWave + l)];
-      const int row = (int)(e >> 8), col = (int)(e & 0xffu);
-      L.F[row * PE + col] = res[k];
-      atomicOr(&now[row], 1ull << col);
-      if (row >= K && row < K + TE && col >= K && col < K + TE) {
-        changed++;
-        last = (uint32_t)i;
-        zone |= 1u;
-        if (i == K) zone |= zone_bits(row - K, col - K);
+      for (int q = 0; q < kPer; ++q) {
+        if (q > 0 && n <= (uint32_t)(p * kPart + q * kWave)) break;
+        const uint32_t idx = (uint32_t)(q * kWave + l);
+        const uint32_t e = (uint32_t)(p * kPart) + idx < n ? (uint32_t)list[idx] : 0u;
+        ent[p * kPer + q] = e;
+        f[p * kPer + q] = (uint32_t)L.key[at((int)(e >> 6), (int)(e & 63u))];
       }
+      wave_sync();
     }
-    wave_sync();
+    __syncthreads();  // every source is read, the round's masks are clear
+    if (L.any[i & 1] == 0u) break;
+#pragma unroll
+    for (int q = 0; q < kParts * kPer; ++q) {
+      if (n <= (uint32_t)(q * kWave)) break;
+      if ((uint32_t)(q * kWave + l) < n) push<CONN, kWide, WPB>(L, now, ent[q], f[q], q0);
+    }
+    __syncthreads();
   }
+  const uint32_t c = (uint32_t)__popcll(L.chg[K & 1][row] & mine & own);
+  changed += c;
+  if (c) last = (uint32_t)K;
 }
 
 // Region change mask (one 64-bit word per region row, bit = region column)
 // of the pixels that changed in the last round of step m-1.  Every such pixel
 // lies in a tile visited in step m-1, which recorded its last-round changes
 // (`record_changes`) under that step's parity with stamp m-1; a tile whose
-// stamp differs did not change.  Lane = region row: the stamps and row words
-// of three tiles (left neighbour, own column, right neighbour).  Split in two
-// so that the loads can be issued before the region load and waited for with
-// it.
+// stamp differs did not change.  One wave, lane = region row: the stamps and
+// row words of three tiles (left neighbour, own column, right neighbour).
+// Split in two so that the loads are in flight with the region's.
 struct PrevChanges {
-  uint32_t stamp[3], word[3];
+  uint32_t stamp[3];
+  unsigned long long word[3];
 };
 
 __device__ __forceinline__ void prev_step_issue(const EdtArgs& a, const TileRef& tr, uint32_t m, PrevChanges& pc) {
   const EdtJob& j = tr.j;
-  const int l = lane();
   const uint32_t par = (m - 1u) & 1u;
-  const int y = tr.ty * TE - K + l;
-  const bool row_ok = l < RP && y >= 0 && y < j.h;
+  const int y = tr.ty * TE - K + lane();
+  const bool row_ok = y >= 0 && y < j.h;
   const int ty = row_ok ? y / TE : 0, ly = row_ok ? y - ty * TE : 0;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const int tx = tr.tx + d - 1;
     pc.stamp[d] = 0u;
-    pc.word[d] = 0u;
+    pc.word[d] = 0ull;
     if (row_ok && tx >= 0 && tx < j.tiles_x) {
       const uint32_t u = j.tile_base + (uint32_t)(ty * j.tiles_x + tx);
       pc.stamp[d] = cload(a.stamps + (size_t)par * a.ntiles + u);
-      pc.word[d] = cload(a.marks + ((size_t)par * a.ntiles + u) * 32u + (uint32_t)ly);
+      pc.word[d] = cload(a.marks + ((size_t)par * a.ntiles + u) * kEdtMarkWords + (uint32_t)ly);
     }
   }
 }
 
 __device__ __forceinline__ void prev_step_finish(uint32_t m, const PrevChanges& pc, unsigned long long* M) {
-  const int l = lane();
   unsigned long long v = 0;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
@@ -379,32 +382,42 @@ __device__ __forceinline__ void prev_step_finish(uint32_t m, const PrevChanges& 
     // region column rx <-> tile column rx - K - (d - 1) * TE
     v |= d == 0 ? (w >> (TE - K)) : (d == 1 ? (w << K) : ((w & ((1ull << K) - 1ull)) << (K + TE)));
   }
-  if (l < RP) M[l] = v;
-  wave_sync();
+  M[lane()] = v;
 }
 
 // Record this visit's last-round changes of the tile (rows and columns
-// [K, K + TE) of the round-K mask `M`) and stamp them with step m.
-__device__ void record_changes(const EdtArgs& a, uint32_t t, uint32_t m, const unsigned long long* M) {
+// [K, K + TE) of the round-K mask word `m` of region row lane()) and stamp
+// them with step `step`.
+__device__ __forceinline__ void record_changes(const EdtArgs& a, uint32_t t, uint32_t step, unsigned long long m) {
   const int l = lane();
-  const uint32_t par = m & 1u;
-  if (l < TE)
-    cstore(a.marks + ((size_t)par * a.ntiles + t) * 32u + (uint32_t)l, (uint32_t)((M[K + l] >> K) & ((1ull << TE) - 1ull)));
-  if (l == 0) cstore(a.stamps + (size_t)par * a.ntiles + t, m);
+  const uint32_t par = step & 1u;
+  if (l >= K && l < K + TE)
+    cstore(a.marks + ((size_t)par * a.ntiles + t) * kEdtMarkWords + (uint32_t)(l - K), (m & kTileCols) >> K);
+  if (l == 0) cstore(a.stamps + (size_t)par * a.ntiles + t, step);
 }
 
-// Store the tile (region rows and columns [K, K + TE)) from S to `dst`.
-__device__ void store_tile(const uint32_t* S, uint32_t* dst, const TileRef& tr) {
+// Store the tile (region rows and columns [K, K + TE)) to `dst`.
+template <int WPB>
+__device__ __forceinline__ void store_tile(const WgLds<WPB>& L, uint32_t* dst, const TileRef& tr) {
   const EdtJob& j = tr.j;
   const int y0 = tr.ty * TE, x0 = tr.tx * TE;
   const int row1 = y0 + TE < j.h ? y0 + TE : j.h;
   const __amdgpu_buffer_rsrc_t rs = rows_rsrc(dst, j, y0, row1 - y0);
-  for (int idx = lane(); idx < TE * TE; idx += kWave) {
-    const int cy = idx / TE, cx = idx - cy * TE;
+  constexpr int kCpr = TE / 4;
+  for (int idx = local_copy((int)threadIdx.x); idx < TE * kCpr; idx += kWave * WPB) {
+    const int cy = idx / kCpr, cx = 4 * (idx - cy * kCpr);
     const int y = y0 + cy, x = x0 + cx;
-    if (y < j.h && x < j.w)
-      __builtin_amdgcn_raw_buffer_store_b32(S[(cy + K) * PE + cx + K], rs,
-                                            ((uint32_t)cy * (uint32_t)j.w + (uint32_t)x) * 4u, 0, kSc1);
+    if (y >= j.h || x >= j.w) continue;
+    const unsigned long long* k = &L.key[at(cy + K, cx + K)];
+    const v4u v = {(uint32_t)k[0], (uint32_t)k[1], (uint32_t)k[2], (uint32_t)k[3]};
+    const uint32_t off = ((uint32_t)cy * (uint32_t)j.w + (uint32_t)x) * 4u;
+    if (x + 4 <= j.w) {
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4i, v), rs, off, 0, kSc1);
+    } else {
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+        if (x + b < j.w) __builtin_amdgcn_raw_buffer_store_b32(v[b], rs, off + 4u * b, 0, kSc1);
+    }
   }
 }
 
@@ -448,97 +461,111 @@ __device__ __forceinline__ void mark_reach(const EdtArgs& a, WaveStage& s, const
              a.ovf);
 }
 
-// Initial state (features carry themselves, everything else none) in both
-// buffers, the contour-feature count (Algorithm 6's initial queue), and the
-// first step's list: round 1 changes exactly the non-features next to a
-// feature, so their tiles and the neighbours within K pixels are listed.  The
-// contour features are every tile's step-0 change record, from which the
-// first step's round 1 takes its active pixels.  One wave per tile; the binary
-// region (tile and one-pixel halo) is staged in LDS.  The flags, counts and
-// stamps must be zero beforehand.
+// Initial state (features carry themselves, everything else none), the
+// contour-feature count (Algorithm 6's initial queue), and the first step's
+// list: round 1 changes exactly the non-features next to a feature, so their
+// tiles and the neighbours within K pixels are listed.  The contour features
+// are every tile's step-0 change record, from which the first step's round 1
+// takes its sources.  The flags, counts and stamps must be zero beforehand.
+//
+// A workgroup per tile, a wave per kRowsPerWave rows, lane = column (lane 0
+// the column before the tile): a row is two wave-uniform 64-bit masks, its
+// features and its other pixels, and all tests are shifts and ORs of masks.
+//
+// Both buffers need the initial state where the first step does not visit; a
+// tile with a round-1 change lists itself, and its visit writes the second.
 template <int CONN, bool kWide>
 __global__ __launch_bounds__(256) void k_init(EdtArgs a) {
-  constexpr int BR = TE + 2;  // binary region side
-  constexpr int BP = BR + 2;  // byte pitch
-  __shared__ uint8_t binl[kWavesPerBlock][BR * BP];
-  __shared__ uint32_t stage_mem[kWavesPerBlock][16];
-  const int w = threadIdx.x / kWave;
-  const uint32_t t = blockIdx.x * kWavesPerBlock + w;
-  if (t >= a.ntiles) return;
+  constexpr int kRowsPerWave = TE / 4;
+  __shared__ uint32_t stage_mem[16];
+  __shared__ uint32_t zone_sh, contour_sh;
+  static_assert(TE % 4 == 0 && TE + 2 <= 64, "four waves, a lane per column and one to each side");
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), l = lane();
+  if (threadIdx.x == 0) zone_sh = contour_sh = 0u;
+  const uint32_t t = blockIdx.x;
   const TileRef tr = tile_ref(a, t);
   const EdtJob& j = tr.j;
-  const int y0 = tr.ty * TE, x0 = tr.tx * TE;
-  uint8_t* B = binl[w];
-  // Region bytes: 1 = feature, 0 = other or outside the image.
-  for (int idx = lane(); idx < BR * BR; idx += kWave) {
-    const int ry = idx / BR, rx = idx - ry * BR;
-    const int y = y0 - 1 + ry, x = x0 - 1 + rx;
-    B[ry * BP + rx] = (y >= 0 && y < j.h && x >= 0 && x < j.w && j.bin[(size_t)y * (uint32_t)j.w + (uint32_t)x] == 0) ? 1 : 0;
-  }
-  wave_sync();
-  const int x = lane() & 31, yb = lane() >> 5;
-  const int qx = x0 + x;
-  uint32_t contour = 0, zone = 0;
-  uint32_t* rec = a.marks + (size_t)t * 32u;  // step 0's record (parity 0; the stamps are zero)
-  for (int y = yb; y < TE; y += 2) {
-    const int qy = y0 + y;
-    bool ct = false;
-    if (x < TE && qy < j.h && qx < j.w) {
-      const uint8_t* c = &B[(y + 1) * BP + x + 1];
-      const bool feat = c[0] != 0;
-      int nf = c[-BP] + c[BP] + c[-1] + c[1];
-      int nin = (qy > 0) + (qy + 1 < j.h) + (qx > 0) + (qx + 1 < j.w);
-      if (CONN == 8) {
-        nf += c[-BP - 1] + c[-BP + 1] + c[BP - 1] + c[BP + 1];
-        nin += (qy > 0 && qx > 0) + (qy > 0 && qx + 1 < j.w) + (qy + 1 < j.h && qx > 0) + (qy + 1 < j.h && qx + 1 < j.w);
-      }
-      const uint32_t v = feat ? pack_yx(qy, qx) : Coord<kWide>::none;
-      const size_t p = j.pix_base + (size_t)qy * (uint32_t)j.w + (uint32_t)qx;
-      a.feat0[p] = v;
-      a.feat1[p] = v;
-      ct = feat && nf < nin;  // a feature with a non-feature neighbour
-      contour += ct ? 1u : 0u;
-      if (!feat && nf > 0) zone |= 1u | zone_bits(y, x);
-    }
-    // Round 0's changes as round 1 sees them: only the contour features
-    // offer anything new (a feature keeps itself; a pixel away from every
-    // feature stays none).  Lanes 0..31 hold row y, lanes 32..63 row y + 1.
-    const uint64_t bm = ballot(ct);
-    if (lane() == 0 || lane() == 32) cstore(rec + y, lane() == 0 ? (uint32_t)bm : (uint32_t)(bm >> 32));
-  }
-  const uint32_t tot = readlane(wave_incl_sum(contour), kWave - 1);
-  uint32_t z = 0;
+  const int y0 = tr.ty * TE + w * kRowsPerWave, x = tr.tx * TE - 1 + l;
+  const bool in_x = x >= 0 && x < j.w && l < TE + 2;
+  const unsigned long long cols = ballot(in_x);
+  uint8_t px[kRowsPerWave + 2];
 #pragma unroll
-  for (int b = 0; b < 9; ++b)
-    if (ballot((zone >> b) & 1u)) z |= 1u << b;
-  if (lane() == 0) {
-    stat_add(a.stats, kStatSeeds, tot);
-    stat_add(a.stats, kStatItems, tot);  // the first frontier
+  for (int k = 0; k < kRowsPerWave + 2; ++k) {
+    const int y = y0 - 1 + k;
+    px[k] = in_x && y >= 0 && y < j.h ? j.bin[(size_t)y * (uint32_t)j.w + (uint32_t)x] : (uint8_t)1;
   }
-  WaveStage st = {stage_mem[w], 16u, 0u};
-  const Next nx = next_frontier(a, 0u);  // step 1's list
-  mark_reach(a, st, nx, tr, z);
-  shard_flush(st, nx.list, nx.count, a.ntiles, nx.flags, a.ovf);
+  // Per row (k = 0: the row above): feature mask, and the mask of other pixels.
+  unsigned long long feat[kRowsPerWave + 2], rest[kRowsPerWave + 2];
+#pragma unroll
+  for (int k = 0; k < kRowsPerWave + 2; ++k) {
+    const int y = y0 - 1 + k;
+    feat[k] = ballot(px[k] == 0);
+    rest[k] = (y >= 0 && y < j.h) ? cols & ~feat[k] : 0ull;
+  }
+  const unsigned long long own = ((1ull << TE) - 1ull) << 1;  // the tile's columns
+  unsigned long long* rec = a.marks + (size_t)t * kEdtMarkWords;  // step 0's record (parity 0; the stamps are zero)
+  uint32_t contour = 0, zone = 0;
+#pragma unroll
+  for (int k = 1; k <= kRowsPerWave; ++k) {
+    auto near = [&](const unsigned long long (&m)[kRowsPerWave + 2]) {  // pixels with a marked neighbour
+      if (CONN == 4) return m[k - 1] | m[k + 1] | (m[k] << 1) | (m[k] >> 1);
+      const unsigned long long v = m[k - 1] | m[k] | m[k + 1];
+      return (v << 1) | (v >> 1) | m[k - 1] | m[k + 1];
+    };
+    // Round 0's changes as round 1 sees them: only the contour features offer
+    // anything new (a feature keeps itself; a pixel away from every feature
+    // stays none).
+    const unsigned long long ct = feat[k] & near(rest) & own, first = rest[k] & near(feat) & own;
+    const int row = w * kRowsPerWave + k - 1;
+    contour += (uint32_t)__popcll(ct);
+    zone |= zone_bits(first >> 1, row);
+    if (l == 0) cstore(rec + row, ct >> 1);
+  }
+  __syncthreads();
+  if (l == 0) {
+    if (zone) atomicOr(&zone_sh, zone);
+    if (contour) atomicAdd(&contour_sh, contour);
+  }
+  __syncthreads();
+  zone = zone_sh;
+#pragma unroll
+  for (int k = 1; k <= kRowsPerWave; ++k) {
+    const int y = y0 - 1 + k;
+    if (y < j.h && ((cols & own) >> l & 1ull)) {
+      const uint32_t v = px[k] == 0 ? pack_yx(y, x) : Coord<kWide>::none;
+      const size_t p = j.pix_base + (size_t)y * (uint32_t)j.w + (uint32_t)x;
+      a.feat0[p] = v;
+      if (!(zone & 1u)) a.feat1[p] = v;
+    }
+  }
+  if (w == 0) {
+    if (l == 0) {
+      stat_add(a.stats, kStatSeeds, contour_sh);
+      stat_add(a.stats, kStatItems, contour_sh);  // the first frontier
+    }
+    WaveStage st = {stage_mem, 16u, 0u};
+    const Next nx = next_frontier(a, 0u);  // step 1's list
+    mark_reach(a, st, nx, tr, zone);
+    shard_flush(st, nx.list, nx.count, a.ntiles, nx.flags, a.ovf);
+  }
 }
 
-// WPB waves per workgroup; five workgroups of four waves (or two of eight)
-// fit a CU's registers and LDS.  A step's tiles are shared by the waves of a
-// workgroup (WgShare).
+// A workgroup of WPB waves per tile visit; four workgroups of four waves (or
+// three of eight) fit a CU's LDS.
 template <int CONN, bool kWide, int WPB>
-__global__ __launch_bounds__(64 * WPB, WPB == 4 ? 5 : 2) void k_rounds(EdtArgs a) {
-  __shared__ WaveLds lds[WPB];
-  __shared__ uint32_t stage_mem[WPB][kStageCap];
+__global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
+  __shared__ WgLds<WPB> L;
+  __shared__ uint32_t stage_mem[kStageCap];
   __shared__ uint32_t cnt[kShards];
-  __shared__ uint32_t last_sh;
+  __shared__ uint32_t last_sh;  // the visit's last round with a change
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  WaveLds& L = lds[w];
   const uint32_t depth = a.stage_depth > 0u && a.stage_depth < (uint32_t)kStageCap ? a.stage_depth : (uint32_t)kStageCap;
-  WaveStage s = {stage_mem[w], depth, 0u};
-  const uint32_t gw = blockIdx.x * WPB + (uint32_t)w, nw = gridDim.x * WPB;
-  if (threadIdx.x == 0) last_sh = 0u;
+  WaveStage s = {stage_mem, depth, 0u};  // wave 0's
+  for (int i = (int)threadIdx.x; i < P * P; i += kWave * WPB) L.key[i] = 0ull;  // the ring stays so
+  if (threadIdx.x == 0) last_sh = L.any[0] = L.any[1] = 0u;
   uint32_t gen = 0, nclk = 0;
   unsigned long long changed = 0, visits = 0;
-  uint32_t last_round = 0;  // this wave's last round with a change
+  uint32_t last_round = 0;  // this workgroup's last round with a change (wave 0)
   clock_stamp(a.clock, nclk);
   for (uint32_t m = 1;; ++m) {
     // Every workgroup reads the same words: nothing writes them between the
@@ -563,59 +590,76 @@ __global__ __launch_bounds__(64 * WPB, WPB == 4 ? 5 : 2) void k_rounds(EdtArgs a
     const uint32_t* lists = a.lists + (size_t)par * kShards * a.ntiles;
     uint32_t* flg = a.flags + (size_t)par * a.ntiles;
     const Next nx = next_frontier(a, m);
-    // Items are dealt round-robin over the waves of the grid: workgroup
-    // pooling, and items kept on the XCD that listed them, were both measured
-    // slower here (1.36 and 1.38 against 1.34 ms on the 4096^2 workload).
-    // The next item's list entry is loaded while the current tile is visited.
-    uint32_t t_next = gw < n ? shard_item(lists, a.ntiles, cnt, gw) : 0u;
-    for (uint32_t i = gw; i < n; i += nw) {
-      const uint32_t t = t_next;
-      if (i + nw < n) t_next = shard_item(lists, a.ntiles, cnt, i + nw);
-      if (lane() == 0) cstore(flg + t, 0u);
+    // Items are dealt round-robin over the workgroups of the grid; the next
+    // item's list entry is loaded while the current tile is visited.
+    uint32_t t_next = blockIdx.x < n ? shard_item(lists, a.ntiles, cnt, blockIdx.x) : 0u;
+    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
+      const uint32_t t = readlane(t_next, 0);
+      if (i + gridDim.x < n) t_next = shard_item(lists, a.ntiles, cnt, i + gridDim.x);
       const TileRef tr = tile_ref(a, t);
       PrevChanges pc;
-      prev_step_issue(a, tr, m, pc);
-      load_region<kWide>(rd, tr, L.F);
-      prev_step_finish(m, pc, L.chg[0]);
-      uint32_t c = 0, zone = 0, lr = 0;
-      relax_steps<CONN, kWide>(L, tr, c, zone, lr);
-      record_changes(a, t, m, L.chg[K & 1]);
+      if (w == 0) {
+        if (lane() == 0) cstore(flg + t, 0u);
+        prev_step_issue(a, tr, m, pc);
+      }
+      load_region<kWide, WPB>(rd, tr, L);
+      if (w == 0) prev_step_finish(m, pc, L.chg[0]);
+      __syncthreads();
+      uint32_t c = 0, lr = 0;
+      relax_steps<CONN, kWide, WPB>(L, tr, c, lr);
       changed += c;
-      visits++;
-      uint32_t z = 0;
-#pragma unroll
-      for (int b = 0; b < 9; ++b)
-        if (ballot((zone >> b) & 1u)) z |= 1u << b;
-      uint32_t lw = 0;  // the wave's last round with a change (lr is 0..K per lane)
-      for (uint32_t v = (uint32_t)K; v > 0u; --v)
-        if (ballot(lr >= v) != 0u) {
-          lw = v;
-          break;
-        }
-      if (lw) last_round = umax32(last_round, (m - 1u) * (uint32_t)K + lw);
-      store_tile(L.F, wr, tr);
-      mark_reach(a, s, nx, tr, z);
-      wave_sync();  // LDS is reloaded by the next visit
+      if (lr) atomicMax(&last_sh, lr);
+      store_tile<WPB>(L, wr, tr);
+      __syncthreads();
+      if (w == 0) {
+        visits++;
+        const unsigned long long mk = L.chg[K & 1][lane()];
+        record_changes(a, t, m, mk);
+        const uint32_t lw = readlane(last_sh, 0);
+        wave_sync();
+        if (lane() == 0) last_sh = 0u;
+        if (lw) last_round = umax32(last_round, (m - 1u) * (uint32_t)K + lw);
+        const int row = lane() - K;
+        uint32_t z = any_zone(row >= 0 && row < TE ? zone_bits((mk & kTileCols) >> K, row) : 0u);
+        if (lw) z |= 1u;
+        mark_reach(a, s, nx, tr, z);
+      }
+      __syncthreads();  // LDS is reloaded by the next visit
     }
-    shard_flush(s, nx.list, nx.count, a.ntiles, nx.flags, a.ovf);
+    if (w == 0) shard_flush(s, nx.list, nx.count, a.ntiles, nx.flags, a.ovf);
     if (!grid_barrier(a.bar, gen, a.stats)) return;
     clock_stamp(a.clock, nclk);
   }
-  // Both buffers now agree everywhere; write the outputs.
-  const uint32_t* fin = a.feat0;
-  const uint32_t stride = gridDim.x * blockDim.x;
+  // Both buffers now agree everywhere; write the outputs.  A wave takes 256
+  // pixels of a row at a time, four per lane.
+  const uint32_t nw = gridDim.x * WPB;
   for (uint32_t jj = 0; jj < a.njobs; ++jj) {
-    const EdtJob& j = a.njobs == 1u ? a.job0 : a.jobs[jj];
-    const uint32_t npx = (uint32_t)j.h * (uint32_t)j.w;
-    for (uint32_t p = blockIdx.x * blockDim.x + threadIdx.x; p < npx; p += stride) {
-      const uint32_t f = cload(fin + j.pix_base + p);
-      if (f == Coord<kWide>::none) {
-        j.sqdist[p] = -1;
-        j.nearest[p] = -1;
+    const EdtJob j = uniform(a.njobs == 1u ? a.job0 : a.jobs[jj]);
+    const uint32_t segs = ((uint32_t)j.w + 255u) / 256u, items = segs * (uint32_t)j.h;
+    for (uint32_t i = blockIdx.x * WPB + (uint32_t)w; i < items; i += nw) {
+      const uint32_t y = i / segs, x = (i - y * segs) * 256u + 4u * (uint32_t)lane();
+      if (x >= (uint32_t)j.w) continue;
+      const __amdgpu_buffer_rsrc_t rf = rows_rsrc(a.feat0, j, (int)y, 1, kStatePad);
+      const __amdgpu_buffer_rsrc_t rd = make_rsrc(j.sqdist + (size_t)y * (uint32_t)j.w, (uint32_t)j.w * 4u);
+      const __amdgpu_buffer_rsrc_t rn = make_rsrc(j.nearest + (size_t)y * (uint32_t)j.w, (uint32_t)j.w * 4u);
+      const v4u f = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rf, 4u * x, 0, kSc1));
+      v4i d, nr;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const bool none = f[b] == Coord<kWide>::none;
+        d[b] = none ? -1 : (int)Coord<kWide>::d2(pack_yx((int)y, (int)x + b), f[b]);
+        nr[b] = none ? -1 : (int)((f[b] >> 16) * (uint32_t)j.w + (f[b] & 0xffffu));
+      }
+      if (x + 4u <= (uint32_t)j.w) {
+        __builtin_amdgcn_raw_buffer_store_b128(d, rd, 4u * x, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(nr, rn, 4u * x, 0, 0);
       } else {
-        const uint32_t y = p / (uint32_t)j.w, x = p - y * (uint32_t)j.w;
-        j.sqdist[p] = (int32_t)Coord<kWide>::d2(pack_yx((int)y, (int)x), f);
-        j.nearest[p] = (int32_t)((f >> 16) * (uint32_t)j.w + (f & 0xffffu));
+#pragma unroll
+        for (int b = 0; b < 3; ++b)
+          if (x + (uint32_t)b < (uint32_t)j.w) {
+            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)d[b], rd, 4u * (x + (uint32_t)b), 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b32((uint32_t)nr[b], rn, 4u * (x + (uint32_t)b), 0, 0);
+          }
       }
     }
   }
@@ -623,13 +667,13 @@ __global__ __launch_bounds__(64 * WPB, WPB == 4 ? 5 : 2) void k_rounds(EdtArgs a
   if (lane() == 0) {
     stat_add(a.stats, kStatItems, changed);  // pixels changed in a round join the next frontier
     stat_add(a.stats, kStatUpdates, changed);
-    stat_add(a.stats, kStatSweeps, visits);
-    atomicMax(&last_sh, last_round);
+    if (w == 0) {
+      stat_add(a.stats, kStatSweeps, visits);
+      // Rounds: the last round in which any pixel changed -- a maximum, kept in
+      // shard 0 so that the host's sum over the shards leaves it unchanged.
+      if (last_round) atomic_max(a.stats + kStatRounds, (unsigned long long)last_round);
+    }
   }
-  __syncthreads();
-  // Rounds: the last round in which any pixel changed -- a maximum, kept in
-  // shard 0 so that the host's sum over the shards leaves it unchanged.
-  if (threadIdx.x == 0 && last_sh) atomic_max(a.stats + kStatRounds, (unsigned long long)last_sh);
 }
 
 // Image of every global tile, by binary search over the images' first tiles.
@@ -660,8 +704,7 @@ int edt_launch(const EdtArgs& a, int conn, int persistent_blocks, hipStream_t st
     *err = "flag reset launch failed";
     return -1;
   }
-  // eight XCD parts of ceil(ntiles / 8) tiles, kWavesPerBlock tiles per workgroup
-  const uint32_t init_blocks = (a.ntiles + kWavesPerBlock - 1) / kWavesPerBlock;
+  const uint32_t init_blocks = a.ntiles;
   rec->begin(4, stream);
   if (conn == 8 && !a.wide)
     hipLaunchKernelGGL((k_init<8, false>), dim3(init_blocks), dim3(256), 0, stream, a);
@@ -690,7 +733,7 @@ int edt_launch(const EdtArgs& a, int conn, int persistent_blocks, hipStream_t st
     *err = "occupancy query failed";
     return -1;
   }
-  uint32_t blocks = persistent_grid(fn, per_cu, cus, wpb == 4 ? 5 : 2);
+  uint32_t blocks = persistent_grid(fn, per_cu, cus, wpb == 4 ? 4 : 2);
   if (persistent_blocks > 0 && (uint32_t)persistent_blocks < blocks) blocks = (uint32_t)persistent_blocks;
   EdtArgs args = a;
   void* kargs[] = {&args};

@@ -10,8 +10,9 @@ struct GridBarrier;
 
 // Tile geometry shared by the host plans and the kernels.
 constexpr int kMrTile = 64;   // reconstruction tiles: 64 x 64 pixels
-constexpr int kEdtHalo = 4;   // EDT rounds per tile visit (= halo width; 8 measured slower)
-constexpr int kEdtTile = 26;  // EDT tiles: 26 x 26 pixels (a 34 x 34 region with the halo)
+constexpr int kEdtHalo = 8;   // EDT rounds per tile visit (= halo width)
+constexpr int kEdtTile = 48;  // EDT tiles: 48 x 48 pixels (a 64 x 64 region with the halo)
+constexpr int kEdtMarkWords = kEdtTile;  // 64-bit words of a tile's change record, one per row
 constexpr size_t kEdtStatePad = 256;  // bytes after each EDT state buffer (16-byte loads may cross the end)
 
 // One reconstruction image of a launch.
@@ -82,7 +83,7 @@ struct EdtArgs {
   uint32_t* flags;            // [2][ntiles] tile on the round's list, per round parity
   uint32_t* lists;            // [2][8 shards][ntiles] tile lists per round parity
   uint32_t* stamps;           // [2][ntiles] step of the tile's last visit, per step parity (0 = none)
-  uint32_t* marks;            // [2][ntiles][32] that visit's last-round change mask, one word per tile row
+  unsigned long long* marks;  // [2][ntiles][kEdtMarkWords] that visit's last-round change mask
   uint32_t* counts;           // [3 round slots][8 shards][64] list fill levels (256 B apart)
   uint32_t* ovf;              // never set: a list holds each tile once
   uint32_t stage_depth;       // work-list items staged per wave before a flush (0 = the LDS maximum)
