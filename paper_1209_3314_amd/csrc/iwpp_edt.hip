@@ -44,14 +44,17 @@
 // to list the sources and 0.9 k to push them, 5 k to store and list tiles --
 // which four workgroups per CU (40 KB of keys each) hide in part, and to the
 // slowest visit of each step.  Measured (30% features, rounds kernel): 4096^2
-// 1124 us, 389 x 517 310 us.  Before, a pull over the neighbourhood of every
+// 1050 us, 389 x 517 300 us.  Before, a pull over the neighbourhood of every
 // change (26 x 26 tiles, four rounds a visit, one wave each; eleven
 // evaluations of nine candidates per changed pixel): 1312 and 505 us.
 //
 // The tiles of a step are a work list split into eight sub-lists, one per
-// group of workgroups (one per XCD), appended to with one atomic per flush and
-// consumed evenly by all workgroups in the next step; a per-tile flag keeps a
-// tile on a step's list once.
+// group of workgroups (one per XCD), appended to with one atomic per flush; a
+// per-tile flag keeps a tile on a step's list once.  With more tiles than
+// workgroups, a group visits its own sub-list (the neighbours of what it visited
+// last, in its own L2) and its workgroups take items as they get to them:
+// 4096^2 1190 us a call with items dealt round-robin over all workgroups, 1160
+// with one counter for all, 1117 by group.
 //
 // State in memory is the feature's packed coordinates (y << 16 | x), 4 bytes
 // per pixel.
@@ -67,6 +70,8 @@ constexpr int R = TE + 2 * K;      // region side: one 64-bit mask word per row
 constexpr int P = R + 2;           // LDS pitch: the region has a ring of pixels that never change around it
 constexpr int kStageCap = 64;      // LDS work-list stage (iwpp_options.stage_depth caps it)
 constexpr int kPart = 256;         // sources a wave lists at a time
+constexpr uint32_t kTaken = 32;      // word of a count's cell with the items taken from the step's list
+constexpr uint32_t kNoTile = 0xFFFFFFFFu;
 constexpr uint32_t kMaxSteps = (1u << 20) / K;
 static_assert(R == 64, "one mask bit per region column, one lane per region row");
 static_assert(K % 4 == 0 && TE % 4 == 0, "16-byte chunks must not straddle the image's left edge or a tile's");
@@ -587,6 +592,28 @@ __global__ void k_list(EdtArgs a) {
   }
 }
 
+// An item beyond the dealt ones of another group's sub-list (cnt[x] items each,
+// `stride` apart), from the first group after `grp` that has one; one wave.
+// Ends: each pass without an item has seen a counter grow past its sub-list.
+__device__ __forceinline__ uint32_t steal(const uint32_t* lists, uint32_t stride, uint32_t* taken, const uint32_t* cnt,
+                                          uint32_t grp) {
+  const uint32_t x = (grp + 1u + (uint32_t)lane()) % kXcds, dealt = xcd_groups(x);
+  const bool other = lane() < (int)kXcds - 1 && cnt[x] > dealt;
+  if (ballot(other) == 0ull) return kNoTile;
+  for (;;) {
+    const unsigned long long left = ballot(other && dealt + cload(taken + 64u * x) < cnt[x]);
+    if (left == 0ull) return kNoTile;
+    const int src = __builtin_ctzll(left);
+    uint32_t t = kNoTile;
+    if (lane() == src) {
+      const uint32_t i = dealt + atomic_add(taken + 64u * x, 1u);
+      if (i < cnt[x]) t = cload(lists + (size_t)x * stride + i);
+    }
+    t = readlane(t, src);
+    if (t != kNoTile) return t;
+  }
+}
+
 // A workgroup of WPB waves per tile visit; four workgroups of four waves (or
 // three of eight) fit a CU's LDS.
 template <int CONN, bool kWide, int WPB>
@@ -595,6 +622,7 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
   __shared__ uint32_t stage_mem[kStageCap];
   __shared__ uint32_t cnt[kShards];
   __shared__ uint32_t last_sh;  // the visit's last round with a change
+  __shared__ uint32_t next_sh;  // the tile to visit next
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t depth = a.stage_depth > 0u && a.stage_depth < (uint32_t)kStageCap ? a.stage_depth : (uint32_t)kStageCap;
   WaveStage s = {stage_mem, depth, 0u};  // wave 0's
@@ -620,19 +648,42 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
     // The counts of step m+2 are reused: clear them now (they were last read
     // at the start of step m-1 and are next appended to in step m+1, after
     // this step's barrier).
-    if (blockIdx.x == 0 && threadIdx.x < (unsigned)kShards) cstore(shard_count(a.counts, (m + 2u) % 3u, threadIdx.x), 0u);
+    if (blockIdx.x == 0 && threadIdx.x < (unsigned)kShards) {
+      cstore(shard_count(a.counts, (m + 2u) % 3u, threadIdx.x), 0u);
+      cstore(shard_count(a.counts, (m + 2u) % 3u, threadIdx.x) + kTaken, 0u);
+    }
     const uint32_t* rd = (m & 1u) ? a.feat0 : a.feat1;  // buffer (m-1)&1
     uint32_t* wr = (m & 1u) ? a.feat1 : a.feat0;        // buffer m&1
     const uint32_t par = m & 1u;
     const uint32_t* lists = a.lists + (size_t)par * kShards * a.ntiles;
     uint32_t* flg = a.flags + (size_t)par * a.ntiles;
     const Next nx = next_frontier(a, m);
-    // Items are dealt round-robin over the workgroups of the grid; the next
-    // item's list entry is loaded while the current tile is visited.
-    uint32_t t_next = blockIdx.x < n ? shard_item(lists, a.ntiles, cnt, blockIdx.x) : 0u;
-    for (uint32_t i = blockIdx.x; i < n; i += gridDim.x) {
-      const uint32_t t = readlane(t_next, 0);
-      if (i + gridDim.x < n) t_next = shard_item(lists, a.ntiles, cnt, i + gridDim.x);
+    // At most one item per workgroup: item b goes to workgroup b, which spreads
+    // them over the CUs.  Otherwise a group (XCD) takes its own sub-list, where
+    // the neighbours of the tiles it visited last are: the first items by rank,
+    // the others from the sub-list's counter as its workgroups get to them, and
+    // at its end those of the other groups.  The next item is taken while the
+    // current tile is visited.
+    const bool sparse = n <= gridDim.x;
+    const uint32_t grp = blockIdx.x % kXcds, rank = blockIdx.x / kXcds, dealt = xcd_groups(grp);
+    uint32_t* taken = shard_count(a.counts, m % 3u, 0u) + kTaken;
+    uint32_t t = kNoTile;
+    if (sparse) {
+      if (blockIdx.x < n) t = shard_item(lists, a.ntiles, cnt, blockIdx.x);
+    } else if (rank < cnt[grp]) {
+      t = cload(lists + (size_t)grp * a.ntiles + rank);
+    } else {
+      if (w == 0) {
+        const uint32_t t0 = steal(lists, a.ntiles, taken, cnt, grp);
+        if (lane() == 0) next_sh = t0;
+      }
+      __syncthreads();
+      t = next_sh;
+    }
+    t = readlane(t, 0);
+    while (t != kNoTile) {
+      uint32_t i = cnt[grp];
+      if (!sparse && threadIdx.x == 0 && i > dealt) i = dealt + atomic_add(taken + 64u * grp, 1u);
       const TileRef tr = tile_ref(a, t);
       PrevChanges pc;
       if (w == 0) {
@@ -641,11 +692,18 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
       }
       load_region<kWide, WPB>(rd, tr, L);
       if (w == 0) prev_step_finish(m, pc, L.chg[0]);
+      uint32_t t_next = kNoTile;
+      if (threadIdx.x == 0 && i < cnt[grp]) t_next = cload(lists + (size_t)grp * a.ntiles + i);
       __syncthreads();
       uint32_t c = 0, lr = 0;
       relax_steps<CONN, kWide, WPB>(L, tr, c, lr);
       changed += c;
       if (lr) atomicMax(&last_sh, lr);
+      if (w == 0 && !sparse) {
+        t_next = readlane(t_next, 0);
+        if (t_next == kNoTile) t_next = steal(lists, a.ntiles, taken, cnt, grp);
+        if (lane() == 0) next_sh = t_next;
+      }
       store_tile<WPB>(L, wr, tr);
       __syncthreads();
       if (w == 0) {
@@ -661,7 +719,9 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
         if (lw) z |= 1u;
         mark_reach(a, s, nx, tr, z);
       }
+      if (sparse) break;
       __syncthreads();  // LDS is reloaded by the next visit
+      t = readlane(next_sh, 0);
     }
     if (w == 0) shard_flush(s, nx.list, nx.count, a.ntiles, nx.flags, a.ovf);
     if (!grid_barrier(a.bar, gen, a.stats)) return;

@@ -55,3 +55,31 @@ def test_long_runs_of_changes():
                 assert np.array_equal(sq.cpu().numpy(), so) and np.array_equal(nr.cpu().numpy(), no)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("blocks", [1, 3, 8, 9, 20])
+def test_more_tiles_than_workgroups(blocks):
+    """Steps that list more tiles than the grid has workgroups: tiles dealt by
+    group, taken as workgroups get to them, and taken from other groups; with
+    fewer workgroups than groups some groups have none.  One image and a batch."""
+    torch, iw = require_gpu()
+    rng = np.random.default_rng(blocks)
+    imgs = [(rng.random(s) >= d).astype(np.uint8) for s, d in (((400, 500), 0.01), ((49, 300), 0.3), ((700, 60), 0.001))]
+    imgs[2][10, 10] = 0
+    ctx = iw.Context(0, persistent_blocks=blocks)
+    try:
+        announce("edt dealing", blocks)
+        for B in imgs:
+            sq, nr = ctx.edt(torch.from_numpy(B).cuda(), 8)
+            st = ctx.stats()
+            so, no, ost = oracle.edt_rounds(B, 8, return_stats=True)
+            assert st["status"] == 0 and np.array_equal(sq.cpu().numpy(), so) and np.array_equal(nr.cpu().numpy(), no)
+            assert st["rounds"] == ost["rounds"] and st["items"] == ost["items"]
+        out = [[torch.empty(B.shape, dtype=torch.int32, device="cuda") for _ in range(2)] for B in imgs]
+        ctx.run_batch([{"op": "edt", "binary": torch.from_numpy(B).cuda(), "sqdist": sq, "nearest": nr, "conn": 8}
+                       for B, (sq, nr) in zip(imgs, out)])
+        for B, (sq, nr) in zip(imgs, out):
+            so, no = oracle.edt_rounds(B, 8)
+            assert np.array_equal(sq.cpu().numpy(), so) and np.array_equal(nr.cpu().numpy(), no)
+    finally:
+        ctx.close()
