@@ -124,6 +124,7 @@ template <bool kSeed>
 __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = false, const uint8_t* cols = nullptr,
                             uint32_t cols_bytes = 0, uint32_t t = 0) {
   const MrJob& a = tr.j;
+  const int lv = local_copy(lane());
   const int y0 = tr.ty * T, x0 = tr.tx * T;
   // Buffer resources over the image rows the region touches, [yb, ye): offsets
   // stay 32-bit whatever the image size (a 66-row band of a row of up to 2^31
@@ -143,7 +144,7 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
   uint32_t xm[kPerMain], xh[kPerHalo];  // complement of what was read inside the image (erosion), else 0
 #pragma unroll
   for (int k = 0; k < kPerMain; ++k) {
-    const int idx = lane() + k * kWave;
+    const int idx = lv + k * kWave;
     const int c = idx & 3;
     const int y = y0 - 1 + (idx >> 2), xs = x0 + 16 * c;
     const bool ok = idx < kMain && y >= 0 && y < a.h && xs + 16 <= a.w;
@@ -154,17 +155,17 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
   }
   v4u vtop = {0u, 0u, 0u, 0u};
   if (kSeed && fresh_top) {  // wave-uniform; lanes 0..3 hold the row above
-    const int y = y0 - 1, xs = x0 + 16 * (lane() & 3);
-    const bool ok = lane() < 4 && y >= 0 && xs + 16 <= a.w;
+    const int y = y0 - 1, xs = x0 + 16 * (lv & 3);
+    const bool ok = lv < 4 && y >= 0 && xs + 16 <= a.w;
     const uint32_t off = ok ? (uint32_t)(y - yb) * (uint32_t)a.w + (uint32_t)xs : kOutside;
     vtop = __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(ro, off, 0, kSc1));
     // lanes 0..3 load the same chunks as vj[0] (row y0 - 1), so xm[0] applies
-    if (lane() < 4) vj[0] = vtop;
+    if (lv < 4) vj[0] = vtop;
   }
   if (kSeed) {
 #pragma unroll
     for (int k = 0; k < kPerHalo; ++k) {
-      const int idx = lane() + k * kWave;
+      const int idx = lv + k * kWave;
       const int y = y0 - 1 + (idx >> 1);
       const int x = (idx & 1) ? x0 + T : x0 - 1;
       const bool ok = idx < kHalo && y >= 0 && y < a.h && x >= 3 && x < a.w;
@@ -178,7 +179,7 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
     // neighbour's left column (J and I); lanes 0..3 also one corner each:
     // top-left, top-right, bottom-left, bottom-right.
     const __amdgpu_buffer_rsrc_t rc = make_rsrc(cols, cols_bytes);
-    const int l = lane();
+    const int l = local_copy(lane());
     const int tx_n = tr.j.tiles_x, ty_n = tr.j.tiles_y;
     const bool has_l = tr.tx > 0, has_r = tr.tx + 1 < tx_n;
     const uint32_t bl = (t - 1u) * 256u, br = (t + 1u) * 256u;
@@ -197,7 +198,7 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
   }
 #pragma unroll
   for (int k = 0; k < kPerMain; ++k) {
-    const int idx = lane() + k * kWave;
+    const int idx = lv + k * kWave;
     if (idx >= kMain) continue;
     const int ry = idx >> 2, c = idx & 3;
     uint32_t* dj = reinterpret_cast<uint32_t*>(&L.J[lidx(ry - 1, c * 16)]);
@@ -211,7 +212,7 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
   if (kSeed) {
 #pragma unroll
     for (int k = 0; k < kPerHalo; ++k) {
-      const int idx = lane() + k * kWave;
+      const int idx = lv + k * kWave;
       if (idx >= kHalo) continue;
       const int ry = idx >> 1;
       const uint32_t jb = (hj[k] ^ xh[k]) >> 24, ib = (hi[k] ^ xh[k]) >> 24;
@@ -220,7 +221,7 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
       L.I[at] = (uint8_t)ib;
     }
   } else {
-    const int l = lane();
+    const int l = local_copy(lane());
     L.J[lidx(l, -1)] = (uint8_t)hj[0];
     L.I[lidx(l, -1)] = (uint8_t)hi[0];
     L.J[lidx(l, T)] = (uint8_t)hj[1];
@@ -235,7 +236,7 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
     const int nb = rem - 16 * cp, xs = x0 + 16 * cp;
 #pragma unroll
     for (int k = 0; k < (kRows + kWave - 1) / kWave; ++k) {
-      const int ry = lane() + k * kWave;
+      const int ry = lv + k * kWave;
       const int y = y0 - 1 + ry;
       const bool row_ok = ry < kRows && y >= 0 && y < a.h;
       uint32_t bj[15], bi[15];
@@ -272,7 +273,7 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
 // read as 0.
 __device__ void load_frame(const TileRef& tr, WaveLds& L, const uint8_t* cols, uint32_t cols_bytes, uint32_t t) {
   const MrJob& a = tr.j;
-  const int y0 = tr.ty * T, x0 = tr.tx * T, l = lane();
+  const int y0 = tr.ty * T, x0 = tr.tx * T, l = local_copy(lane());
   const int yb = y0 > 0 ? y0 - 1 : 0, ye = y0 + T + 1 < a.h ? y0 + T + 1 : a.h;
   const uint32_t band = (uint32_t)(ye - yb) * (uint32_t)a.w;
   const size_t base = (size_t)yb * (size_t)(uint32_t)a.w;
@@ -338,6 +339,7 @@ __device__ void load_frame(const TileRef& tr, WaveLds& L, const uint8_t* cols, u
 // the image's right edge (see load_region).
 __device__ void load_interior(const TileRef& tr, WaveLds& L) {
   const MrJob& a = tr.j;
+  const int lv = local_copy(lane());
   const int y0 = tr.ty * T, x0 = tr.tx * T;
   const int yb = y0 > 0 ? y0 - 1 : 0, ye = y0 + T + 1 < a.h ? y0 + T + 1 : a.h;
   const uint32_t band = (uint32_t)(ye - yb) * (uint32_t)a.w;
@@ -352,7 +354,7 @@ __device__ void load_interior(const TileRef& tr, WaveLds& L) {
   uint32_t xm[kPer];  // complement of what was read inside the image (erosion), else 0
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int idx = lane() + k * kWave;
+    const int idx = lv + k * kWave;
     const int c = idx & 3;
     const int y = y0 + 1 + (idx >> 2), xs = x0 + 16 * c;
     const bool ok = idx < kChunks && y < a.h && xs + 16 <= a.w;
@@ -363,7 +365,7 @@ __device__ void load_interior(const TileRef& tr, WaveLds& L) {
   }
 #pragma unroll
   for (int k = 0; k < kPer; ++k) {
-    const int idx = lane() + k * kWave;
+    const int idx = lv + k * kWave;
     if (idx >= kChunks) continue;
     const int ry = 1 + (idx >> 2), c = idx & 3;
     uint32_t* dj = reinterpret_cast<uint32_t*>(&L.J[lidx(ry, c * 16)]);
@@ -376,7 +378,7 @@ __device__ void load_interior(const TileRef& tr, WaveLds& L) {
   }
   if (cp >= 0) {  // wave-uniform: only tiles cut by the right edge of the image
     const int nb = rem - 16 * cp, xs = x0 + 16 * cp;
-    const int ry = 1 + lane();
+    const int ry = 1 + lv;
     const int y = y0 + ry;
     const bool row_ok = ry < T - 1 && y < a.h;
     uint32_t bj[15], bi[15];
@@ -407,7 +409,7 @@ __device__ void store_tile(const TileRef& tr, const WaveLds& L) {
   const int ye = y0 + T < a.h ? y0 + T : a.h;  // the tile's rows, as a band of their own (see load_region)
   const __amdgpu_buffer_rsrc_t ro =
       make_rsrc(a.out + (size_t)y0 * (size_t)(uint32_t)a.w, (uint32_t)(ye - y0) * (uint32_t)a.w);
-  for (int idx = lane(); idx < T * 4; idx += kWave) {
+  for (int idx = local_copy(lane()); idx < T * 4; idx += kWave) {
     const int ry = idx >> 2, c = idx & 3;
     const int y = y0 + ry, xs = x0 + c * 16;
     if (y >= a.h || xs >= a.w) continue;
@@ -430,7 +432,7 @@ __device__ void store_tile(const TileRef& tr, const WaveLds& L) {
 // of `cols`: [J left | J right | I left | I right], 64 bytes each.
 __device__ void store_cols(const MrArgs& a, uint32_t t, const WaveLds& L, bool mask) {
   const __amdgpu_buffer_rsrc_t rc = make_rsrc(a.cols + (size_t)t * 256u, 256u);
-  const int l = lane();
+  const int l = local_copy(lane());
   __builtin_amdgcn_raw_buffer_store_b8(L.J[lidx(l, 0)], rc, (uint32_t)l, 0, kSc1);
   __builtin_amdgcn_raw_buffer_store_b8(L.J[lidx(l, T - 1)], rc, 64u + (uint32_t)l, 0, kSc1);
   if (mask) {
@@ -439,22 +441,28 @@ __device__ void store_cols(const MrArgs& a, uint32_t t, const WaveLds& L, bool m
   }
 }
 
-// Rows and columns of the tile that changed since each axis scan last ran
-// (bit = row or column index, wave-uniform).  After a scan in direction D
-// every pixel dominates the offers of its D-predecessors (the pixel before it
-// along D: left for rows forward, right for rows backward, the row above --
-// three pixels with 8-connectivity -- for columns forward, the row below for
-// columns backward), and it keeps dominating them until one of those
-// predecessors rises.  So a scan only needs the 16-wide chunks whose
-// predecessors changed since it last ran, plus any chunk after one that it
-// has just changed; and the tile is locally stable exactly when all four sets
-// are empty (the four scans' predecessors are all eight neighbours, or all
-// four).  Changes made by a row scan are known per row (lane = row) and per
-// chunk of columns; those of a column scan per column and per chunk of rows.
+// Rows and columns of the tile that changed since the scans that could carry
+// the change further last ran (bit = row or column index, wave-uniform).  After
+// a scan in direction D every pixel dominates the offers of its D-predecessors
+// (the pixel before it along D: left for rows forward, right for rows backward,
+// the row above -- three pixels with 8-connectivity -- for columns forward, the
+// row below for columns backward), and it keeps dominating them until one of
+// those predecessors rises.  So a scan only needs the 16-wide chunks whose
+// predecessors changed since it last ran, plus any chunk after one that it has
+// just changed; and the tile is locally stable exactly when all sets are empty
+// (the four scans' predecessors are all eight neighbours, or all four).
+//
+// Along a line of its own (rows; columns with 4-connectivity) a scan in one
+// direction leaves intact what the other has reached: with x dominating its
+// left offers and x' the result of the backward scan, x'[k-1] <= max(x[k-1],
+// x'[k]), so min(x'[k-1], I[k]) <= max(x[k], x'[k]) = x'[k].  So rows need one
+// set for both directions, and a scan never adds to its own axis' set.  With
+// 8-connectivity a column scan's changes do reach the other direction, through
+// the diagonals.
 struct Dirty {
   uint64_t r_cf, r_cb;  // rows changed since the last column scan forward / backward
-  uint64_t c_rf, c_rb;  // columns changed since the last row scan forward / backward
-  __device__ bool empty() const { return (r_cf | r_cb | c_rf | c_rb) == 0ull; }
+  uint64_t c_r;         // columns changed since the last row scans
+  __device__ bool empty() const { return (r_cf | r_cb | c_r) == 0ull; }
 };
 
 // Apply every halo pixel's offer to the border pixels it touches, once:
@@ -465,7 +473,7 @@ struct Dirty {
 // both.  Sets the rows and the columns that hold a border pixel that rose.
 template <int CONN>
 __device__ void fold_halo(WaveLds& L, uint64_t& rows, uint64_t& cols) {
-  const int l = lane();
+  const int l = local_copy(lane());
   auto offer = [&](int hy0, int hx0, int hy1, int hx1, int hy2, int hx2) {  // max of the halo neighbours
     uint32_t h = L.J[lidx(hy1, hx1)];
     if (CONN == 8) h = umax(h, umax((uint32_t)L.J[lidx(hy0, hx0)], (uint32_t)L.J[lidx(hy2, hx2)]));
@@ -491,18 +499,31 @@ __device__ void fold_halo(WaveLds& L, uint64_t& rows, uint64_t& cols) {
   cols = top | bot | (left ? 1ull : 0ull) | (right ? 1ull << (T - 1) : 0ull);
 }
 
-// One axis scan of the tile in LDS, after `fold_halo`: the halo is ignored.
-// Vertical scans walk the rows with lane = column, using the previous row's
-// values of the three (8-conn) or one (4-conn) upper/lower neighbours;
-// horizontal scans walk the columns with lane = row, using the previous
-// column.  Steps are loaded from LDS in chunks of kChunk so the wave pays one
-// LDS latency per chunk rather than per step; a chunk's results are written
-// back if any of them changed, and increases accumulate in `ch`.  A chunk
-// whose predecessors did not change since this scan last ran (`Dirty`), and
-// that follows no chunk this scan changed, is skipped; the chunk after a
-// skipped one reads its carried-in neighbour values from LDS.
+// The two scans of an axis of the tile in LDS, after `fold_halo`: the halo is
+// ignored.  Vertical scans walk the rows with lane = column, using the previous
+// row's values of the three (8-conn) or one (4-conn) upper/lower neighbours;
+// horizontal scans walk the columns with lane = row, using the previous column.
+//
+// A scan is a serial chain -- every step waits for the one before -- of two to
+// five instructions a step, and one wave has 64 of them; four waves per SIMD do
+// not cover the wait.  So the forward and the backward scan of an axis run
+// together, in four passes of one 16-wide chunk each: the forward scan takes
+// chunks 0, 1, 2, 3, the backward scan 3, 2, 1, 0, never the same chunk in one
+// pass, and their independent steps fill each other's waits; a pass also pays
+// its LDS latency once for both (16384^2 with 4-connectivity 1728 -> 1707 us,
+// 4096^2 352 -> 342, 1500 x 1301 213 -> 205, 512^2 with 8 143.5 -> 140.5; the same
+// with the compiler's order of the steps and change tests: 1910, 398, 241, 160).
+// In place: from the third pass on each works on
+// what the other has raised.  Every value is a valid update of the ones it was
+// computed from and at least what either scan alone would give, and on a line
+// the limit is the larger of the two scans, so after a pair the line is stable.
+//
+// A chunk's results are written back if any of them changed.  A chunk whose
+// predecessors did not change since this scan last ran (`Dirty`), and that
+// follows no chunk this scan changed, is skipped; the chunk after a skipped one
+// reads its carried-in neighbour values from LDS.
 constexpr int kChunk = 16;
-static_assert(T == 4 * kChunk, "four chunks per scan");
+static_assert(T == 4 * kChunk, "four chunks per scan: with an even number no pass has both scans on one chunk");
 
 // Predecessor lines of chunk [x0, x0 + 16) in the scan's direction.
 __device__ __forceinline__ uint64_t chunk_preds(int x0, bool forward) {
@@ -510,11 +531,19 @@ __device__ __forceinline__ uint64_t chunk_preds(int x0, bool forward) {
   return forward ? w >> 1 : w << 1;
 }
 
+// d | (a ^ b): collects whether anything changed, one instruction a step.
+__device__ __forceinline__ uint32_t or_diff(uint32_t a, uint32_t b, uint32_t d) {
+  asm("v_bitop3_b32 %0, %1, %2, %0 bitop3:0xbe" : "+v"(d) : "v"(a), "v"(b));
+  return d;
+}
+
 // Row scans (lane = row) on packed words: one step is a byte-selecting max of
 // the old pixel and the previous result, then a byte-selecting min with the
 // mask written into the pixel's byte in place (SDWA with the other bytes
 // preserved), two instructions per pixel with no unpacking or repacking.
 // MR_HSTEP: pixel byte K of word W, previous result in byte PK of word PW.
+// MR_HSTEP2: such a step of each scan, alternating (the instruction between
+// also is the wait state that reading a just-written byte needs).
 #define MR_HSTEP(W, PW, I, K, PK)                                                                       \
   do {                                                                                                  \
     uint32_t m_;                                                                                        \
@@ -527,85 +556,140 @@ __device__ __forceinline__ uint64_t chunk_preds(int x0, bool forward) {
         : "+v"(W)                                                                                       \
         : "v"(m_), "v"(I));                                                                             \
   } while (0)
+#define MR_HSTEP2(W, PW, I, K, PK, W2, PW2, I2, K2, PK2)                                                \
+  do {                                                                                                  \
+    uint32_t m_, m2_;                                                                                   \
+    asm("v_max_u32_sdwa %0, %2, %4 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #K              \
+        " src1_sel:BYTE_" #PK "\n\t"                                                                    \
+        "v_max_u32_sdwa %1, %3, %5 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #K2             \
+        " src1_sel:BYTE_" #PK2 "\n\t"                                                                   \
+        "v_min_u32_sdwa %2, %0, %6 dst_sel:BYTE_" #K " dst_unused:UNUSED_PRESERVE src0_sel:DWORD"      \
+        " src1_sel:BYTE_" #K "\n\t"                                                                     \
+        "v_min_u32_sdwa %3, %1, %7 dst_sel:BYTE_" #K2 " dst_unused:UNUSED_PRESERVE src0_sel:DWORD"     \
+        " src1_sel:BYTE_" #K2                                                                           \
+        : "=&v"(m_), "=&v"(m2_), "+v"(W), "+v"(W2)                                                      \
+        : "v"(PW), "v"(PW2), "v"(I), "v"(I2));                                                          \
+  } while (0)
 
-template <bool kForward, bool kDirty>
-__device__ __forceinline__ void row_scan(WaveLds& L, uint32_t& ch, Dirty& dm) {
-  const int l = lane();
-  uint64_t& mine = kForward ? dm.c_rf : dm.c_rb;
-  uint64_t& other = kForward ? dm.c_rb : dm.c_rf;
-  uint32_t pw = 0;  // word holding the previous result: byte 3 (forward) or byte 0 (backward)
-  bool carried = true;  // pw holds the previous chunk's result (the halo's zero before the first)
-  bool carry = false;   // the previous chunk changed
-  uint32_t acc = 0;
+// MR_HSTEP1: MR_HSTEP2 with the previous results in the same words.
+#define MR_HSTEP1(W, I, K, PK, W2, I2, K2, PK2)                                                         \
+  do {                                                                                                  \
+    uint32_t m_, m2_;                                                                                   \
+    asm("v_max_u32_sdwa %0, %2, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #K              \
+        " src1_sel:BYTE_" #PK "\n\t"                                                                    \
+        "v_max_u32_sdwa %1, %3, %3 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_" #K2             \
+        " src1_sel:BYTE_" #PK2 "\n\t"                                                                   \
+        "v_min_u32_sdwa %2, %0, %4 dst_sel:BYTE_" #K " dst_unused:UNUSED_PRESERVE src0_sel:DWORD"      \
+        " src1_sel:BYTE_" #K "\n\t"                                                                     \
+        "v_min_u32_sdwa %3, %1, %5 dst_sel:BYTE_" #K2 " dst_unused:UNUSED_PRESERVE src0_sel:DWORD"     \
+        " src1_sel:BYTE_" #K2                                                                           \
+        : "=&v"(m_), "=&v"(m2_), "+v"(W), "+v"(W2)                                                      \
+        : "v"(I), "v"(I2));                                                                             \
+  } while (0)
+
+// A scan's state from one chunk to the next.
+struct Carry {
+  uint32_t prev = 0;    // the previous result: rows, the word holding it (byte 3 forward, byte 0 backward)
+  bool carried = true;  // prev is the previous chunk's result (the halo's zero before the first)
+  bool changed = false;  // the previous chunk changed
+};
+
+// One pass of the row scans: the forward scan (kF) on the chunk at column xf
+// and the backward scan (kB) on the one at xb.
+template <bool kF, bool kB>
+__device__ __forceinline__ void row_pass(WaveLds& L, int l, int xf, int xb, Carry& f, Carry& b, uint64_t& rows) {
+  uint32_t* jf = reinterpret_cast<uint32_t*>(&L.J[lidx(l, xf)]);
+  uint32_t* jb = reinterpret_cast<uint32_t*>(&L.J[lidx(l, xb)]);
+  const uint32_t* mf = reinterpret_cast<const uint32_t*>(&L.I[lidx(l, xf)]);
+  const uint32_t* mb = reinterpret_cast<const uint32_t*>(&L.I[lidx(l, xb)]);
+  uint32_t w[4], u[4], ow[4], ou[4], iw[4], iu[4];
+  if (kF && !f.carried) f.prev = jf[-1];
+  if (kB && !b.carried) b.prev = jb[4];
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    if (kF) ow[d] = w[d] = jf[d], iw[d] = mf[d];
+    if (kB) ou[d] = u[d] = jb[d], iu[d] = mb[d];
+  }
+  uint32_t df = 0, db = 0;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    const int e = 3 - d;
+    if (kF && kB) {
+      MR_HSTEP2(w[d], f.prev, iw[d], 0, 3, u[e], b.prev, iu[e], 3, 0);
+      MR_HSTEP1(w[d], iw[d], 1, 0, u[e], iu[e], 2, 3);
+      MR_HSTEP1(w[d], iw[d], 2, 1, u[e], iu[e], 1, 2);
+      MR_HSTEP1(w[d], iw[d], 3, 2, u[e], iu[e], 0, 1);
+    } else if (kF) {
+      MR_HSTEP(w[d], f.prev, iw[d], 0, 3);
+      MR_HSTEP(w[d], w[d], iw[d], 1, 0);
+      MR_HSTEP(w[d], w[d], iw[d], 2, 1);
+      MR_HSTEP(w[d], w[d], iw[d], 3, 2);
+    } else {
+      MR_HSTEP(u[e], b.prev, iu[e], 3, 0);
+      MR_HSTEP(u[e], u[e], iu[e], 2, 3);
+      MR_HSTEP(u[e], u[e], iu[e], 1, 2);
+      MR_HSTEP(u[e], u[e], iu[e], 0, 1);
+    }
+    if (kF) df = or_diff(ow[d], w[d], df), f.prev = w[d];
+    if (kB) db = or_diff(ou[e], u[e], db), b.prev = u[e];
+  }
+  if (kF) {
+    const uint64_t r = ballot(df != 0u);
+    f.carried = true;
+    f.changed = r != 0ull;
+    if (f.changed) {  // a chunk that changed nothing is not written back
+#pragma unroll
+      for (int d = 0; d < 4; ++d) jf[d] = w[d];
+      rows |= r;
+    }
+  }
+  if (kB) {
+    const uint64_t r = ballot(db != 0u);
+    b.carried = true;
+    b.changed = r != 0ull;
+    if (b.changed) {
+#pragma unroll
+      for (int d = 0; d < 4; ++d) jb[d] = u[d];
+      rows |= r;
+    }
+  }
+}
+
+// Both row scans; returns the rows that changed.
+template <bool kDirty>
+__device__ __forceinline__ uint64_t row_pair(WaveLds& L, int l, uint64_t dirty) {
+  Carry f, b;
+  uint64_t rows = 0ull;
 #pragma unroll 1
   for (int c = 0; c < T / kChunk; ++c) {
-    const int x0 = (kForward ? c : T / kChunk - 1 - c) * kChunk;
-    if (kDirty && !carry && (mine & chunk_preds(x0, kForward)) == 0ull) {
-      carried = false;
+    const int xf = c * kChunk, xb = T - kChunk - xf;
+    if (!kDirty) {
+      row_pass<true, true>(L, l, xf, xb, f, b, rows);
       continue;
     }
-    uint32_t* jp = reinterpret_cast<uint32_t*>(&L.J[lidx(l, x0)]);
-    const uint32_t* ip = reinterpret_cast<const uint32_t*>(&L.I[lidx(l, x0)]);
-    if (!carried) pw = kForward ? jp[-1] : jp[4];
-    uint32_t w0 = jp[0], w1 = jp[1], w2 = jp[2], w3 = jp[3];
-    const uint32_t o0 = w0, o1 = w1, o2 = w2, o3 = w3;
-    const uint32_t i0 = ip[0], i1 = ip[1], i2 = ip[2], i3 = ip[3];
-    if (kForward) {
-      MR_HSTEP(w0, pw, i0, 0, 3); MR_HSTEP(w0, w0, i0, 1, 0); MR_HSTEP(w0, w0, i0, 2, 1); MR_HSTEP(w0, w0, i0, 3, 2);
-      MR_HSTEP(w1, w0, i1, 0, 3); MR_HSTEP(w1, w1, i1, 1, 0); MR_HSTEP(w1, w1, i1, 2, 1); MR_HSTEP(w1, w1, i1, 3, 2);
-      MR_HSTEP(w2, w1, i2, 0, 3); MR_HSTEP(w2, w2, i2, 1, 0); MR_HSTEP(w2, w2, i2, 2, 1); MR_HSTEP(w2, w2, i2, 3, 2);
-      MR_HSTEP(w3, w2, i3, 0, 3); MR_HSTEP(w3, w3, i3, 1, 0); MR_HSTEP(w3, w3, i3, 2, 1); MR_HSTEP(w3, w3, i3, 3, 2);
-      pw = w3;
-    } else {
-      MR_HSTEP(w3, pw, i3, 3, 0); MR_HSTEP(w3, w3, i3, 2, 3); MR_HSTEP(w3, w3, i3, 1, 2); MR_HSTEP(w3, w3, i3, 0, 1);
-      MR_HSTEP(w2, w3, i2, 3, 0); MR_HSTEP(w2, w2, i2, 2, 3); MR_HSTEP(w2, w2, i2, 1, 2); MR_HSTEP(w2, w2, i2, 0, 1);
-      MR_HSTEP(w1, w2, i1, 3, 0); MR_HSTEP(w1, w1, i1, 2, 3); MR_HSTEP(w1, w1, i1, 1, 2); MR_HSTEP(w1, w1, i1, 0, 1);
-      MR_HSTEP(w0, w1, i0, 3, 0); MR_HSTEP(w0, w0, i0, 2, 3); MR_HSTEP(w0, w0, i0, 1, 2); MR_HSTEP(w0, w0, i0, 0, 1);
-      pw = w0;
-    }
-    carried = true;
-    const uint32_t d = (o0 ^ w0) | (o1 ^ w1) | (o2 ^ w2) | (o3 ^ w3);
-    const uint64_t rows = ballot(d != 0u);
-    carry = rows != 0ull;
-    if (carry) {  // a chunk that changed nothing is not written back
-      jp[0] = w0;
-      jp[1] = w1;
-      jp[2] = w2;
-      jp[3] = w3;
-      if (kDirty) {
-        dm.r_cf |= rows;
-        dm.r_cb |= rows;
-        other |= 0xFFFFull << x0;
-      }
-    }
-    acc |= d;
+    const bool do_f = f.changed || (dirty & chunk_preds(xf, true)) != 0ull;
+    const bool do_b = b.changed || (dirty & chunk_preds(xb, false)) != 0ull;
+    if (!do_f) f.carried = f.changed = false;
+    if (!do_b) b.carried = b.changed = false;
+    if (do_f && do_b)
+      row_pass<true, true>(L, l, xf, xb, f, b, rows);
+    else if (do_f)
+      row_pass<true, false>(L, l, xf, xb, f, b, rows);
+    else if (do_b)
+      row_pass<false, true>(L, l, xf, xb, f, b, rows);
   }
-  mine = 0ull;
-  ch |= acc;
   wave_sync();
+  return rows;
 }
 #undef MR_HSTEP
-
-// min(v, byte B of w) for a byte-sized v (SDWA selects the mask byte).
-template <int B>
-__device__ __forceinline__ uint32_t min_byte(uint32_t v, uint32_t w) {
-  uint32_t r;
-  if (B == 0)
-    asm("v_min_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(r) : "v"(v), "v"(w));
-  else if (B == 1)
-    asm("v_min_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(v), "v"(w));
-  else if (B == 2)
-    asm("v_min_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(r) : "v"(v), "v"(w));
-  else
-    asm("v_min_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(r) : "v"(v), "v"(w));
-  return r;
-}
+#undef MR_HSTEP1
+#undef MR_HSTEP2
 
 // The tile's mask column of this lane, four rows per word (row 4w + b in byte
 // b of ic[w]): the mask does not change during a visit, so the column scans
 // take it from registers and read only J from LDS.
 __device__ __forceinline__ void load_mask_column(const WaveLds& L, uint32_t (&ic)[T / 4]) {
-  const int l = lane();
+  const int l = local_copy(lane());
 #pragma unroll
   for (int w = 0; w < T / 4; ++w) {
     const uint32_t b0 = L.I[lidx(4 * w, l)], b1 = L.I[lidx(4 * w + 1, l)], b2 = L.I[lidx(4 * w + 2, l)],
@@ -614,150 +698,226 @@ __device__ __forceinline__ void load_mask_column(const WaveLds& L, uint32_t (&ic
   }
 }
 
-template <int CONN, bool kForward, bool kDirty, int C>
-__device__ __forceinline__ void column_chunk(WaveLds& L, uint32_t& ch, Dirty& dm, const uint32_t (&ic)[T / 4],
-                                             uint32_t& prev, bool& carried, bool& carry) {
-  const int l = lane();
-  constexpr int y0 = (kForward ? C : T / kChunk - 1 - C) * kChunk;
-  uint64_t& mine = kForward ? dm.r_cf : dm.r_cb;
-  uint64_t& other = kForward ? dm.r_cb : dm.r_cf;
-  if (kDirty && !carry && (mine & chunk_preds(y0, kForward)) == 0ull) {
-    carried = false;
-    return;
+// One step of the column scans: old values V, previous row's results P, the row's
+// mask in byte B of M; the new value goes to N.  J <= I throughout, so
+// min(max(J, offers), I) is the update.  With 8-connectivity the two lane shifts
+// of the diagonal offers are fused into the max (DPP with zero fill); a DPP read
+// of a just-written register needs two wait states, so a step begins with
+// collecting the previous step's changes (P against its old value O, into D).
+// `column_step2` is a step of each scan, alternating.
+#define MR_MIN(D, S, I, B) "v_min_u32_sdwa " D ", " S ", " I " dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_" B "\n\t"
+#define MR_DIFF(D, N, V) "v_bitop3_b32 " D ", " N ", " V ", " D " bitop3:0xbe\n\t"
+#define MR_SHR(D, P, V) "v_max_u32_dpp " D ", " P ", " V " wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+#define MR_SHL(D, P, V) "v_max_u32_dpp " D ", " P ", " V " wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
+#define MR_MAX(D, A, B) "v_max_u32 " D ", " A ", " B "\n\t"
+
+template <int CONN, int B>
+__device__ __forceinline__ void column_step2(uint32_t& vf, uint32_t& pf, uint32_t& of, uint32_t& df, uint32_t mf,
+                                             uint32_t& vb, uint32_t& pb, uint32_t& ob, uint32_t& db, uint32_t mb) {
+  uint32_t nf, nb, tf, tb;
+#define MR_STEP8(BF, BB)                                                                                            \
+  asm(MR_DIFF("%4", "%6", "%12") MR_DIFF("%5", "%7", "%13") MR_SHR("%0", "%6", "%8") MR_SHR("%1", "%7", "%9")         \
+          MR_SHL("%2", "%6", "%6") MR_SHL("%3", "%7", "%7") MR_MAX("%0", "%0", "%2") MR_MAX("%1", "%1", "%3")         \
+              MR_MIN("%0", "%0", "%10", BF) MR_MIN("%1", "%1", "%11", BB)                                             \
+      : "=&v"(nf), "=&v"(nb), "=&v"(tf), "=&v"(tb), "+v"(df), "+v"(db)                                                \
+      : "v"(pf), "v"(pb), "v"(vf), "v"(vb), "v"(mf), "v"(mb), "v"(of), "v"(ob))
+#define MR_STEP4(BF, BB)                                                                                             \
+  asm(MR_DIFF("%2", "%4", "%10") MR_DIFF("%3", "%5", "%11") MR_MAX("%0", "%4", "%6") MR_MAX("%1", "%5", "%7")          \
+          MR_MIN("%0", "%0", "%8", BF) MR_MIN("%1", "%1", "%9", BB)                                                    \
+      : "=&v"(nf), "=&v"(nb), "+v"(df), "+v"(db)                                                                       \
+      : "v"(pf), "v"(pb), "v"(vf), "v"(vb), "v"(mf), "v"(mb), "v"(of), "v"(ob))
+  if constexpr (CONN == 8) {
+    if constexpr (B == 0) MR_STEP8("0", "3");
+    if constexpr (B == 1) MR_STEP8("1", "2");
+    if constexpr (B == 2) MR_STEP8("2", "1");
+    if constexpr (B == 3) MR_STEP8("3", "0");
+  } else {
+    if constexpr (B == 0) MR_STEP4("0", "3");
+    if constexpr (B == 1) MR_STEP4("1", "2");
+    if constexpr (B == 2) MR_STEP4("2", "1");
+    if constexpr (B == 3) MR_STEP4("3", "0");
   }
-  if (!carried) prev = L.J[lidx(kForward ? y0 - 1 : y0 + kChunk, l)];
-  uint32_t vj[kChunk];
-  const uint32_t ch0 = ch;
-#pragma unroll
-  for (int k = 0; k < kChunk; ++k) {
-    const int s = kForward ? y0 + k : y0 + kChunk - 1 - k;
-    vj[k] = L.J[lidx(s, l)];
-  }
-#pragma unroll
-  for (int k = 0; k < kChunk; ++k) {
-    const int s = kForward ? y0 + k : y0 + kChunk - 1 - k;
-    const uint32_t iw = ic[s / 4];
-    uint32_t m;
-    if (CONN == 8) {
-      // The two lane shifts of the diagonal offers are fused into the max
-      // (DPP with zero fill; the s_nop gives the two wait states a DPP read
-      // of a just-written register needs).
-      uint32_t ml, mr;
-      asm("s_nop 1\n\t"
-          "v_max_u32_dpp %0, %2, %3 wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:1\n\t"
-          "v_max_u32_dpp %1, %2, %2 wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:1"
-          : "=&v"(ml), "=&v"(mr)
-          : "v"(prev), "v"(vj[k]));
-      m = umax(ml, mr);
-    } else {
-      m = umax(vj[k], prev);
-    }
-    // J <= I throughout, so min(max(J, offers), I) is the update.
-    uint32_t nv;
-    switch (s & 3) {
-      case 0: nv = min_byte<0>(m, iw); break;
-      case 1: nv = min_byte<1>(m, iw); break;
-      case 2: nv = min_byte<2>(m, iw); break;
-      default: nv = min_byte<3>(m, iw); break;
-    }
-    // Values only rise, so the sum of increases is nonzero iff something changed.
-    ch += nv - vj[k];
-    vj[k] = nv;
-    prev = nv;
-  }
-  carried = true;
-  const uint64_t cols = ballot(ch != ch0);
-  carry = cols != 0ull;
-  if (carry) {  // a chunk that changed nothing is not written back
-#pragma unroll
-    for (int k = 0; k < kChunk; ++k) {
-      const int s = kForward ? y0 + k : y0 + kChunk - 1 - k;
-      L.J[lidx(s, l)] = (uint8_t)vj[k];
-    }
-    if (kDirty) {
-      dm.c_rf |= cols;
-      dm.c_rb |= cols;
-      other |= 0xFFFFull << y0;
-    }
-  }
-  asm volatile("" ::: "memory");  // keep chunks apart: bounded register use
+#undef MR_STEP8
+#undef MR_STEP4
+  of = vf, ob = vb;
+  vf = pf = nf, vb = pb = nb;
 }
 
-template <int CONN, bool kVertical, bool kForward, bool kDirty>
-__device__ __forceinline__ void scan(WaveLds& L, uint32_t& ch, Dirty& dm, const uint32_t (&ic)[T / 4]) {
-  if (!kVertical) {
-    row_scan<kForward, kDirty>(L, ch, dm);
-    return;
+// A step of one scan alone (8-connectivity: the other had nothing to do).
+template <int B>
+__device__ __forceinline__ void column_step1(uint32_t& v, uint32_t& p, uint32_t& o, uint32_t& d, uint32_t m) {
+  uint32_t n, t;
+#define MR_STEP(BF)                                                                                              \
+  asm(MR_DIFF("%2", "%3", "%6") "s_nop 0\n\t" MR_SHR("%0", "%3", "%4") MR_SHL("%1", "%3", "%3") MR_MAX("%0", "%0", "%1") \
+          MR_MIN("%0", "%0", "%5", BF)                                                                           \
+      : "=&v"(n), "=&v"(t), "+v"(d)                                                                              \
+      : "v"(p), "v"(v), "v"(m), "v"(o))
+  if constexpr (B == 0) MR_STEP("0");
+  if constexpr (B == 1) MR_STEP("1");
+  if constexpr (B == 2) MR_STEP("2");
+  if constexpr (B == 3) MR_STEP("3");
+#undef MR_STEP
+  o = v;
+  v = p = n;
+}
+#undef MR_MIN
+#undef MR_DIFF
+#undef MR_SHR
+#undef MR_SHL
+#undef MR_MAX
+
+template <int CONN, int C, int K, bool kF, bool kB>
+__device__ __forceinline__ void column_steps(uint32_t (&vf)[kChunk], uint32_t (&vb)[kChunk], uint32_t& df, uint32_t& db,
+                                             const uint32_t (&ic)[T / 4], Carry& f, Carry& b, uint32_t of,
+                                             uint32_t ob) {
+  if constexpr (K < kChunk) {
+    constexpr int sf = C * kChunk + K, sb = T - 1 - sf;  // this step's rows
+    static_assert((sf & 3) + (sb & 3) == 3, "the backward scan's mask byte mirrors the forward scan's");
+    if constexpr (kF && kB)
+      column_step2<CONN, (sf & 3)>(vf[K], f.prev, of, df, ic[sf / 4], vb[K], b.prev, ob, db, ic[sb / 4]);
+    else if constexpr (kF)
+      column_step1<(sf & 3)>(vf[K], f.prev, of, df, ic[sf / 4]);
+    else
+      column_step1<(sb & 3)>(vb[K], b.prev, ob, db, ic[sb / 4]);
+    column_steps<CONN, C, K + 1, kF, kB>(vf, vb, df, db, ic, f, b, of, ob);
+  } else {
+    if constexpr (kF) df = or_diff(of, f.prev, df);
+    if constexpr (kB) db = or_diff(ob, b.prev, db);
   }
-  uint32_t prev = 0;
-  bool carried = true;  // prev holds the previous chunk's last row (the halo's zero before the first)
-  bool carry = false;   // the previous chunk changed
-  column_chunk<CONN, kForward, kDirty, 0>(L, ch, dm, ic, prev, carried, carry);
-  column_chunk<CONN, kForward, kDirty, 1>(L, ch, dm, ic, prev, carried, carry);
-  column_chunk<CONN, kForward, kDirty, 2>(L, ch, dm, ic, prev, carried, carry);
-  column_chunk<CONN, kForward, kDirty, 3>(L, ch, dm, ic, prev, carried, carry);
-  (kForward ? dm.r_cf : dm.r_cb) = 0ull;
+}
+
+// Pass C of the column scans: the forward scan (kF) on rows [16 C, 16 C + 16)
+// and the backward scan (kB) on the mirrored chunk.
+template <int CONN, int C, bool kF, bool kB>
+__device__ __forceinline__ void column_pass(WaveLds& L, int l, const uint32_t (&ic)[T / 4], Carry& f, Carry& b, uint64_t& cols) {
+  constexpr int yf = C * kChunk, yb = T - 1 - yf;  // the scans' first rows
+  uint32_t vf[kChunk], vb[kChunk], df = 0, db = 0;
+  if (kF && !f.carried) f.prev = L.J[lidx(yf - 1, l)];
+  if (kB && !b.carried) b.prev = L.J[lidx(yb + 1, l)];
+#pragma unroll
+  for (int k = 0; k < kChunk; ++k) {
+    if (kF) vf[k] = L.J[lidx(yf + k, l)];
+    if (kB) vb[k] = L.J[lidx(yb - k, l)];
+  }
+  column_steps<CONN, C, 0, kF, kB>(vf, vb, df, db, ic, f, b, f.prev, b.prev);
+  if (kF) {
+    const uint64_t c = ballot(df != 0u);
+    f.carried = true;
+    f.changed = c != 0ull;
+    if (f.changed) {  // a chunk that changed nothing is not written back
+#pragma unroll
+      for (int k = 0; k < kChunk; ++k) L.J[lidx(yf + k, l)] = (uint8_t)vf[k];
+      cols |= c;
+    }
+  }
+  if (kB) {
+    const uint64_t c = ballot(db != 0u);
+    b.carried = true;
+    b.changed = c != 0ull;
+    if (b.changed) {
+#pragma unroll
+      for (int k = 0; k < kChunk; ++k) L.J[lidx(yb - k, l)] = (uint8_t)vb[k];
+      cols |= c;
+    }
+  }
+  asm volatile("" ::: "memory");  // keep passes apart: bounded register use
+}
+
+// Both column scans; returns the columns that changed.  With 8-connectivity one
+// after the other: together they would leave the diagonal offers of each
+// other's last two passes for another pair (16384^2: 1618 us, one after the other
+// 1537).
+template <int CONN, bool kDirty, int C, bool kF, bool kB>
+__device__ __forceinline__ void column_chunk(WaveLds& L, int l, const uint32_t (&ic)[T / 4], Carry& f, Carry& b, Dirty& dm,
+                                             uint64_t& cols) {
+  if constexpr (kDirty) {
+    static_assert(kF != kB, "dirty chunks are tracked by scan");
+    constexpr int y0 = kF ? C * kChunk : T - kChunk - C * kChunk;
+    Carry& c = kF ? f : b;
+    if (!c.changed && ((kF ? dm.r_cf : dm.r_cb) & chunk_preds(y0, kF)) == 0ull) {
+      c.carried = false;
+      return;
+    }
+    column_pass<CONN, C, kF, kB>(L, l, ic, f, b, cols);
+    if (c.changed) (kF ? dm.r_cb : dm.r_cf) |= 0xFFFFull << y0;
+  } else {
+    column_pass<CONN, C, kF, kB>(L, l, ic, f, b, cols);
+  }
+}
+
+template <int CONN, bool kDirty, bool kF, bool kB>
+__device__ __forceinline__ uint64_t column_scan(WaveLds& L, int l, const uint32_t (&ic)[T / 4], Dirty& dm) {
+  Carry f, b;
+  uint64_t cols = 0ull;
+  column_chunk<CONN, kDirty, 0, kF, kB>(L, l, ic, f, b, dm, cols);
+  column_chunk<CONN, kDirty, 1, kF, kB>(L, l, ic, f, b, dm, cols);
+  column_chunk<CONN, kDirty, 2, kF, kB>(L, l, ic, f, b, dm, cols);
+  column_chunk<CONN, kDirty, 3, kF, kB>(L, l, ic, f, b, dm, cols);
+  if constexpr (kF != kB) (kF ? dm.r_cf : dm.r_cb) = 0ull;
+  else dm.r_cf = dm.r_cb = 0ull;
   wave_sync();
+  return cols;
 }
 
 // Sweep the tile in LDS until it is locally stable, or `max_it` iterations.
-// One iteration is the four axis scans of Algorithm 5 in its order: row-wise
-// forward (N^{+,0}), column-wise forward (N^{0,+}), row-wise backward
-// (N^{-,0}), column-wise backward (N^{0,-}).  Every step is one elementary
-// update J(p) <- max(J(p), J(q in the scan's neighbour set)) ^ I(p), so the
-// tile never leaves [J ^ I, rho_I(J)].  Halo pixels are sources only, and
-// `fold_halo` applies all their offers before the first scan.
+// One iteration is the four axis scans of Algorithm 5, as two pairs: row-wise
+// forward (N^{+,0}) and backward (N^{-,0}), column-wise forward (N^{0,+}) and
+// backward (N^{0,-}).  Every step is one elementary update J(p) <- max(J(p),
+// J(q in the scan's neighbour set)) ^ I(p), so the tile never leaves [J ^ I,
+// rho_I(J)].  Halo pixels are sources only, and `fold_halo` applies all their
+// offers before the first scan.
 //
 // When the sweep stops.  With 8-connectivity the scans track what changed
 // (`Dirty`): a scan with nothing to do costs nothing, and the tile is stable
 // when no scan has anything left.  `all_dirty`: the tile as loaded is not
 // known to be locally stable (a seed-pass tile, a tile the sweep cap stopped,
 // a full round); otherwise its last visit left it stable and only the border
-// pixels the halo raised start dirty.  With 4-connectivity changes spread
-// over most of a tile and the bookkeeping measured slower (1.86 against
-// 1.84 ms on the 16384^2 workload, against 1.54 and 1.65 ms with
-// 8-connectivity): there four consecutive scans that change nothing (one of
-// each direction, in any phase) mean every pixel dominates each of its
-// neighbours' offers; after a scan that changed pixels three suffice, since
-// that scan left its own direction satisfied and nothing has risen since.  Returns true if the tile is locally stable;
+// pixels the halo raised start dirty.  With 4-connectivity both pairs leave
+// their lines stable, so the tile is when a pair after the first changes
+// nothing.  `columns_first` picks the first pair, e.g. the one that carries a
+// raised halo side into the tile.  Returns true if the tile is locally stable;
 // `changed` tells whether any pixel rose.
 template <int CONN>
-__device__ bool sweep_tile(WaveLds& L, int max_it, uint32_t& iters, bool& changed, bool all_dirty, int start = 0) {
+__device__ bool sweep_tile(WaveLds& L, int max_it, uint32_t& iters, bool& changed, bool all_dirty, bool columns_first = false) {
   constexpr bool kDirty = CONN == 8;
   uint64_t rows, cols;
   fold_halo<CONN>(L, rows, cols);
   changed = (rows | cols) != 0ull;
   Dirty dm;
   if (all_dirty || !kDirty) {
-    dm.r_cf = dm.r_cb = dm.c_rf = dm.c_rb = ~0ull;
+    dm.r_cf = dm.r_cb = dm.c_r = ~0ull;
   } else {
     dm.r_cf = dm.r_cb = rows;
-    dm.c_rf = dm.c_rb = cols;
+    dm.c_r = cols;
   }
   uint32_t ic[T / 4];
   load_mask_column(L, ic);
-  int quiet = 0;        // consecutive scans that changed nothing (4-connectivity)
-  bool scanned = false;  // some scan of this visit changed a pixel
-  // `start` picks the first scan (0 rows forward, 1 columns forward, 2 rows
-  // backward, 3 columns backward), e.g. the one that carries a raised halo
-  // side into the tile; the cyclic order is Algorithm 5's.
-  for (int n = 0; n < 4 * max_it; ++n) {
+  const int l = local_copy(lane());
+  for (int n = 0; n < 2 * max_it; ++n) {
     if (kDirty && dm.empty()) return true;
-    if ((n & 3) == 0) iters++;
-    uint32_t ch = 0;
-    switch ((start + n) & 3) {
-      case 0: if (!kDirty || dm.c_rf) scan<CONN, false, true, kDirty>(L, ch, dm, ic); break;
-      case 1: if (!kDirty || dm.r_cf) scan<CONN, true, true, kDirty>(L, ch, dm, ic); break;
-      case 2: if (!kDirty || dm.c_rb) scan<CONN, false, false, kDirty>(L, ch, dm, ic); break;
-      default: if (!kDirty || dm.r_cb) scan<CONN, true, false, kDirty>(L, ch, dm, ic); break;
+    if ((n & 1) == 0) iters++;
+    bool rose = false;
+    if (((n & 1) != 0) == columns_first) {
+      if (!kDirty || dm.c_r) {
+        const uint64_t r = row_pair<kDirty>(L, l, dm.c_r);
+        dm.c_r = 0ull;
+        dm.r_cf |= r;
+        dm.r_cb |= r;
+        rose = r != 0ull;
+      }
+    } else if (!kDirty || (dm.r_cf | dm.r_cb)) {
+      uint64_t c = 0ull;
+      if constexpr (kDirty) {
+        if (dm.r_cf) c |= column_scan<CONN, true, true, false>(L, l, ic, dm);
+        if (dm.r_cb) c |= column_scan<CONN, true, false, true>(L, l, ic, dm);
+      } else {
+        c = column_scan<CONN, false, true, true>(L, l, ic, dm);
+      }
+      dm.c_r |= c;
+      rose = c != 0ull;
     }
-    if (ballot(ch != 0u) != 0u) {
-      changed = true;
-      scanned = true;
-      quiet = 0;
-    } else if (!kDirty && ++quiet == (scanned ? 3 : 4)) {
-      return true;
-    }
+    if (rose) changed = true;
+    if (!kDirty && !rose && n > 0) return true;
   }
   return kDirty && dm.empty();
 }
@@ -775,7 +935,7 @@ __device__ __forceinline__ bool halo_raisable(const WaveLds& L, int qy, int qx, 
 // 6 bottom-left, 7 bottom-right.  o* are the border values before the visit.
 template <int CONN>
 __device__ uint32_t border_marks(const WaveLds& L, uint32_t ot, uint32_t ob, uint32_t ol, uint32_t orr) {
-  const int l = lane();
+  const int l = local_copy(lane());
   const uint32_t nt = L.J[lidx(0, l)], nb = L.J[lidx(T - 1, l)];
   const uint32_t nl = L.J[lidx(l, 0)], nr = L.J[lidx(l, T - 1)];
   bool t = false, b = false, lf = false, rt = false;
@@ -814,7 +974,7 @@ __device__ uint32_t border_marks(const WaveLds& L, uint32_t ot, uint32_t ob, uin
 // way, because only its halo changed since.  Wave-uniform bit mask.
 template <int CONN>
 __device__ uint32_t border_raisable(const WaveLds& L) {
-  const int l = lane();
+  const int l = local_copy(lane());
   bool rt = false, rb = false, rl = false, rr = false;
   // p on row 0 (halo row -1), row T-1 (halo row T), column 0 (halo column -1), column T-1 (halo column T)
   const uint32_t pt = L.J[lidx(0, l)], it = L.I[lidx(0, l)];
@@ -848,7 +1008,7 @@ __device__ __forceinline__ uint32_t gval(uint32_t j, uint32_t i) { return j < i 
 
 template <int CONN>
 __device__ bool lds_dirty(const WaveLds& L, uint32_t& seeds) {
-  const int l = lane();
+  const int l = local_copy(lane());
   const int hc = l == 0 ? -1 : T;  // fill column: lane 0 uses column -1, lane 63 column 64
   uint32_t jp = L.J[lidx(-1, l)], ip = L.I[lidx(-1, l)], fjp = L.J[lidx(-1, hc)], fip = L.I[lidx(-1, hc)];
   uint32_t jc = L.J[lidx(0, l)], ic = L.I[lidx(0, l)], fjc = L.J[lidx(0, hc)], fic = L.I[lidx(0, hc)];
@@ -929,85 +1089,73 @@ __device__ void mark_reach(WaveStage& s, const Next& nx, const TileRef& tr, uint
   shard_mark(s, want, tr.j.tile_base + (uint32_t)(ny * tr.j.tiles_x + nx_), nx.flags, nx.list, nx.count, nx.cap, nx.lost);
 }
 
-// Round-0 visit: the seed pass of one tile (load from the clamped marker,
-// sweep, write back) and its marks for round 1.
-//
-// In strip order (`fresh_top`: the tile above was written by this wave just
-// before) the halo row above comes from the output; `below_next`: the tile
-// below is this wave's next tile and will read this one's result, so it need
-// not be flagged for this tile's bottom edge.
-template <int CONN>
-__device__ void seed_visit(const MrArgs& a, WaveLds& L, WaveStage& s, const Next& nx, uint32_t t, uint32_t& iters,
-                           bool fresh_top = false, bool below_next = false) {
-  const TileRef tr = tile_ref(a, t);
-  if (fresh_top) drain();  // this wave's stores of the tile above are complete
-  load_region<true>(tr, L, fresh_top);
-  const int l = lane();
-  const uint32_t ot = L.J[lidx(0, l)], ob = L.J[lidx(T - 1, l)];
-  const uint32_t ol = L.J[lidx(l, 0)], orr = L.J[lidx(l, T - 1)];
-  uint32_t it = 0;
-  bool changed;
-  const bool stable = sweep_tile<CONN>(L, a.seed_sweeps, it, changed, true);
-  iters += it;
-  store_tile(tr, L);
-  store_cols(a, t, L, true);
-  if (lane() == 0) cstore(a.unsettled + t, stable ? 0u : 1u);
-  uint32_t m = border_marks<CONN>(L, ot, ob, ol, orr);
-  if (below_next) m &= ~2u;  // bit 1: bottom
-  mark_reach(s, nx, tr, m, !stable);
-}
+// A wave's counters over the kernel.
+struct Counters {
+  uint32_t visits = 0, iters = 0, seeds = 0;
+};
 
-// One propagation visit: load the tile and its halo, sweep to local
-// stability, write back, and flag the neighbouring tiles a border change can
-// raise (and the tile itself if the sweep cap stopped it).  A tile that its
-// last visit left stable needs work only if its new halo can raise its
-// border (`border_raisable`); with `check` (full rounds) the whole tile is
-// tested instead.
+enum class Visit { kSeed, kListed, kCheck };
+
+// One visit of a tile: load it with its halo, sweep to local stability, write
+// back, and flag the neighbouring tiles a border change can raise (and the
+// tile itself if the sweep cap stopped it).
+//
+// kSeed (round 0): the tile comes from the clamped marker.  In strip order
+// (`fresh_top`: the tile above was written by this wave just before) the halo
+// row above comes from the output; `below_next`: the tile below is this wave's
+// next tile and will read this one's result, so it need not be flagged for this
+// tile's bottom edge.
+//
+// kListed: a tile that its last visit left stable needs work only if its new
+// halo can raise its border (`border_raisable`); kCheck (full rounds): the
+// whole tile is tested instead.
+//
+// One function for the three, called from one place: the sweep is some 40 KB of
+// code, and a copy for each would not fit the instruction cache together.
 template <int CONN>
-__device__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStage& s, const Next& nx, uint32_t t, bool check,
-                           uint32_t& visits, uint32_t& iters, uint32_t& seeds) {
+__device__ __forceinline__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStage& s, const Next& nx, uint32_t t,
+                                           Visit how, bool fresh_top, bool below_next, Counters& n) {
   const TileRef tr = tile_ref(a, t);
-  int start = 0;
-  bool all_dirty = true;
-  if (check) {
-    load_region<false>(tr, L, false, a.cols, a.ntiles * 256u, t);
-    if (!lds_dirty<CONN>(L, seeds)) return;
+  bool columns_first = false, all_dirty = true;
+  if (how == Visit::kSeed) {
+    if (fresh_top) drain();  // this wave's stores of the tile above are complete
+    load_region<true>(tr, L, fresh_top);
   } else {
-    const uint32_t uns = lane() == 0 ? cload(a.unsettled + t) : 0u;
-    uint32_t sides;
-    if (CONN == 8) {
+    const uint32_t uns = how == Visit::kListed && lane() == 0 ? cload(a.unsettled + t) : 0u;
+    if (CONN == 8 && how == Visit::kListed) {
       // About a third of the listed 8-connected tiles turn out to need no
       // work: load the frame first and the interior only if needed.  Nearly
       // every listed 4-connected tile needs work, and the second round trip
       // measured slower there (1.85 against 1.81 ms): one load.
       load_frame(tr, L, a.cols, a.ntiles * 256u, t);
-      sides = border_raisable<CONN>(L);
-      if (readlane(uns, 0) == 0u && sides == 0u) return;
-      load_interior(tr, L);
     } else {
       load_region<false>(tr, L, false, a.cols, a.ntiles * 256u, t);
-      sides = border_raisable<CONN>(L);
-      if (readlane(uns, 0) == 0u && sides == 0u) return;
     }
-    all_dirty = readlane(uns, 0) != 0u;
-    // First scan: the one moving away from a raisable side (top: columns
-    // forward, bottom: columns backward, left: rows forward, right: rows backward).
-    start = (sides & 1u) ? 1 : (sides & 2u) ? 3 : (sides & 4u) ? 0 : (sides & 8u) ? 2 : 0;
+    if (how == Visit::kCheck) {
+      if (!lds_dirty<CONN>(L, n.seeds)) return;
+    } else {
+      const uint32_t sides = border_raisable<CONN>(L);
+      all_dirty = readlane(uns, 0) != 0u;
+      if (!all_dirty && sides == 0u) return;
+      if (CONN == 8) load_interior(tr, L);
+      columns_first = (sides & 3u) != 0u;  // the scans that lead away from a raisable top or bottom
+    }
   }
-  const int l = lane();
+  const int l = local_copy(lane());
   const uint32_t ot = L.J[lidx(0, l)], ob = L.J[lidx(T - 1, l)];
   const uint32_t ol = L.J[lidx(l, 0)], orr = L.J[lidx(l, T - 1)];
-  uint32_t it = 0;
+  const bool seed = how == Visit::kSeed;
   bool changed;
-  const bool stable = sweep_tile<CONN>(L, a.max_sweeps, it, changed, all_dirty, start);
-  iters += it;
-  visits++;
+  const bool stable =
+      sweep_tile<CONN>(L, seed ? a.seed_sweeps : a.max_sweeps, n.iters, changed, all_dirty, columns_first);
+  if (!seed) n.visits++;
   if (lane() == 0) cstore(a.unsettled + t, stable ? 0u : 1u);
-  if (changed) {
+  if (changed || seed) {
     store_tile(tr, L);
-    store_cols(a, t, L, false);
+    store_cols(a, t, L, seed);
   }
-  const uint32_t m = changed ? border_marks<CONN>(L, ot, ob, ol, orr) : 0u;
+  uint32_t m = changed ? border_marks<CONN>(L, ot, ob, ol, orr) : 0u;
+  if (below_next) m &= ~2u;  // bit 1: bottom
   mark_reach(s, nx, tr, m, !stable);
 }
 
@@ -1038,53 +1186,32 @@ __global__ __launch_bounds__(64 * WPB, 16 / WPB) void k_propagate(MrArgs a) {
   const uint32_t nw = gridDim.x * WPB;  // waves of the grid
   const uint32_t cap = a.list_cap < a.ntiles ? a.list_cap : a.ntiles;
   uint32_t gen = 0, nclk = 0;
-  uint32_t visits = 0, iters = 0, seed_iters = 0, rounds = 0, restarts = 0, seeds = 0, first = 0;
+  uint32_t rounds = 0, restarts = 0, first = 0;
+  Counters n_;
   clock_stamp(a.clock, nclk);
-  {
-    const Next nx = next_frontier(a, 0u);
-    if (a.njobs == 1u) {
-      // Strip order: each wave seeds vertical strips of S tiles top to bottom,
-      // so the flood crosses the horizontal tile edges inside the seed pass.
-      // The strips are shared by the waves of each workgroup (WgShare).
-      const MrJob& j = a.job0;
-      const uint32_t tx_n = (uint32_t)j.tiles_x, ty_n = (uint32_t)j.tiles_y;
-      const uint32_t S = a.seed_strip > 0u ? a.seed_strip : (a.ntiles + nw - 1u) / nw;
-      const uint32_t sy_n = (ty_n + S - 1) / S, nstrips = tx_n * sy_n;
-      const bool cut = (j.w % T) != 0 && (j.w % T) % 16 != 0;  // right-edge tiles read bytes: stale halo there
-      const WgShare share = wg_share(nstrips, &next_sh);
-      for (uint32_t sid; share.take(sid);) {
-        const uint32_t tx = sid % tx_n, ty0 = (sid / tx_n) * S;
-        for (uint32_t k = 0; k < S && ty0 + k < ty_n; ++k) {
-          const bool fresh_col = !(cut && tx + 1 == tx_n);
-          const bool fresh = k > 0 && fresh_col;
-          const bool below = fresh_col && k + 1 < S && ty0 + k + 1 < ty_n;  // the next tile reads this one fresh
-          seed_visit<CONN>(a, L, s, nx, (ty0 + k) * tx_n + tx, seed_iters, fresh, below);
-        }
-      }
-    } else {
-      const WgShare share = wg_share(a.ntiles, &next_sh);
-      for (uint32_t t; share.take(t);) seed_visit<CONN>(a, L, s, nx, t, seed_iters);
-    }
-    shard_flush(s, nx.list, nx.count, nx.cap, nx.flags, nx.lost);
-  }
-  round_work(a.clock, 0u, a.ntiles);
-  bool ok = grid_barrier(a.bar, gen, a.stats);
-  clock_stamp(a.clock, nclk);
-  ok = ok && a.seed_only == 0u;
-  for (uint32_t r = 1; ok; ++r) {
+  // Seed pass, strip order (one image): each wave seeds vertical strips of S
+  // tiles top to bottom, so the flood crosses the horizontal tile edges inside
+  // the seed pass.  The strips are shared by the waves of each workgroup.
+  const bool strips = a.njobs == 1u;
+  const uint32_t S = !strips ? 1u : a.seed_strip > 0u ? a.seed_strip : (a.ntiles + nw - 1u) / nw;
+  for (uint32_t r = 0;; ++r) {
     const uint32_t par = r & 1u;
-    // Every workgroup reads the same words: nothing writes them between the
-    // previous barrier and this read (round r appends for round r+1).
-    shard_counts(a.counts, r % 3u, cap, cnt);
-    if (threadIdx.x == 0) {
-      lost_sh = cload(a.lost + par * 64u);
-      next_sh = 0u;  // last used before the previous barrier
+    bool full = false;
+    uint32_t n = a.ntiles;
+    if (r > 0u) {
+      // Every workgroup reads the same words: nothing writes them between the
+      // previous barrier and this read (round r appends for round r+1).
+      shard_counts(a.counts, r % 3u, cap, cnt);
+      if (threadIdx.x == 0) {
+        lost_sh = cload(a.lost + par * 64u);
+        next_sh = 0u;  // last used before the previous barrier
+      }
+      __syncthreads();
+      n = 0;
+      for (int x = 0; x < kShards; ++x) n += cnt[x];
+      full = lost_sh != 0u;
+      if (!full && n == 0u) break;
     }
-    __syncthreads();
-    uint32_t n = 0;
-    for (int x = 0; x < kShards; ++x) n += cnt[x];
-    const bool full = lost_sh != 0u;
-    if (!full && n == 0u) break;
     round_work(a.clock, r, full ? a.ntiles : n);
     if (r >= kMaxRounds) {  // safety limit: report instead of spinning on a logic error
       if (blockIdx.x == 0 && threadIdx.x == 0) stat_add(a.stats, kStatError, 1ull);
@@ -1103,35 +1230,56 @@ __global__ __launch_bounds__(64 * WPB, 16 / WPB) void k_propagate(MrArgs a) {
     }
     // The counts of round r+2 are reused: clear them now (they were last read
     // in round r-1, and are next appended to in round r+1, after this round's barrier).
-    if (blockIdx.x == 0 && threadIdx.x < (unsigned)kShards) cstore(shard_count(a.counts, (r + 2u) % 3u, threadIdx.x), 0u);
+    if (r > 0u && blockIdx.x == 0 && threadIdx.x < (unsigned)kShards)
+      cstore(shard_count(a.counts, (r + 2u) % 3u, threadIdx.x), 0u);
     const Next nx = next_frontier(a, r);
-    const uint32_t before = visits;
-    if (full) {
-      const WgShare share = wg_share(a.ntiles, &next_sh);
-      for (uint32_t t; share.take(t);) visit_tile<CONN>(a, L, s, nx, t, true, visits, iters, seeds);
-    } else {
-      const uint32_t* lists = a.lists + (size_t)par * kShards * a.ntiles;
-      uint32_t* flg = a.flags + (size_t)par * a.ntiles;
-      // XCD x visits the tiles XCD x listed (a bounded list is one sub-list:
-      // then the whole list is cut over the grid)
-      const bool bounded = a.list_cap < a.ntiles;
-      const WgShare share = bounded ? wg_share(n, &next_sh) : wg_share_lists(cnt, &next_sh);
-      for (uint32_t i; share.take(i);) {
-        const uint32_t t = shard_item(lists, a.ntiles, cnt, i);
-        if (lane() == 0) cstore(flg + t, 0u);
-        visit_tile<CONN>(a, L, s, nx, t, false, visits, iters, seeds);
+    const uint32_t before = n_.visits;
+    const uint32_t* lists = a.lists + (size_t)par * kShards * a.ntiles;
+    uint32_t* flg = a.flags + (size_t)par * a.ntiles;
+    const uint32_t tx_n = (uint32_t)a.job0.tiles_x, ty_n = (uint32_t)a.job0.tiles_y;  // strips only
+    // Items: strips or tiles (seed pass, full round), entries of the lists.
+    // XCD x visits the tiles XCD x listed (a bounded list is one sub-list:
+    // then the whole list is cut over the grid).
+    const uint32_t items = r == 0u && strips ? tx_n * ((ty_n + S - 1u) / S) : full ? a.ntiles : n;
+    const WgShare share = r == 0u || full || a.list_cap < a.ntiles ? wg_share(items, &next_sh) : wg_share_lists(cnt, &next_sh);
+    const Visit how = r == 0u ? Visit::kSeed : full ? Visit::kCheck : Visit::kListed;
+    uint32_t t = 0, left = 0;  // seed pass: the tile, and how many of its strip follow
+    bool fresh = false;
+    for (;;) {
+      if (left > 0u) {
+        --left;
+        t += tx_n;
+      } else {
+        uint32_t i;
+        if (!share.take(i)) break;
+        t = i;
+        if (how == Visit::kListed) {
+          t = shard_item(lists, a.ntiles, cnt, i);
+          t = readlane(t, 0);
+          if (lane() == 0) cstore(flg + t, 0u);
+        } else if (how == Visit::kSeed && strips) {
+          const uint32_t ty0 = i / tx_n * S;
+          t = ty0 * tx_n + i % tx_n;
+          left = (ty0 + S < ty_n ? ty0 + S : ty_n) - ty0 - 1u;
+        }
+        fresh = false;
       }
+      // Right-edge tiles of widths not a multiple of 16 read bytes: stale halo there.
+      const bool below = left > 0u && !(a.job0.w % 16 != 0 && t % tx_n + 1u == tx_n);
+      visit_tile<CONN>(a, L, s, nx, t, how, fresh, below, n_);
+      fresh = below;
     }
     shard_flush(s, nx.list, nx.count, nx.cap, nx.flags, nx.lost);
-    if (r == 1) first = visits - before;
-    rounds++;
-    ok = grid_barrier(a.bar, gen, a.stats);
+    if (r == 1u) first = n_.visits - before;
+    if (r > 0u) rounds++;
+    const bool ok = grid_barrier(a.bar, gen, a.stats);
     clock_stamp(a.clock, nclk);
+    if (!ok || a.seed_only != 0u) break;
   }
   if (lane() == 0) {
     stat_add(a.stats, kStatSeeds, (unsigned long long)first);
-    stat_add(a.stats, kStatItems, visits);
-    stat_add(a.stats, kStatSweeps, iters + seed_iters);
+    stat_add(a.stats, kStatItems, n_.visits);
+    stat_add(a.stats, kStatSweeps, n_.iters);
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     stat_add(a.stats, kStatRounds, rounds);
