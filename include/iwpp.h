@@ -64,7 +64,7 @@ typedef struct {
    * after its global queue overflows (Sec. 3.2, Sec. 5.2.4).  0 = no limit. */
   int64_t mr_list_capacity;
   /* Cap on sweep iterations per tile visit before the tile is re-queued
-   * (0 = 2). */
+   * (0 = 4). */
   int32_t mr_max_sweeps;
   /* Workgroups of the persistent kernels (0 = fill the device). */
   int32_t persistent_blocks;

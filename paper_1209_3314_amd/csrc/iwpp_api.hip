@@ -282,12 +282,16 @@ int32_t launch_group(iwpp_ctx* ctx, const Group& g, uint8_t* scratch, uint8_t* f
     a.ntiles = (uint32_t)g.ntiles;
     const int64_t cap = ctx->opt.mr_list_capacity;
     a.list_cap = (cap > 0 && (uint64_t)cap < g.ntiles) ? (uint32_t)cap : (uint32_t)g.ntiles;
-    // Defaults from measurement on the 16384^2 workloads: a visit that stops
-    // after two sweep iterations and is listed again is cheaper overall than
-    // one swept to stability, since neighbours keep changing its halo; the
+    // Defaults from measurement: a visit that stops after four sweep iterations
+    // and is listed again is cheaper overall than one swept to stability, since
+    // neighbours keep changing its halo, and than one that stops after two and
+    // is loaded again (us with 2, 3, 4, 8: 16384^2 with 4-connectivity 1589,
+    // 1517, 1517, 1535; 4096^2 329, 307, 303, 307; 65536 x 65600 with 8
+    // 16860, 15980, 15850, 15980; 16384^2 with 8 1535, 1533, 1531, 1533).  The
     // seed pass does one iteration with 8-connectivity, two with 4 (whose
-    // paths inside a tile are longer).
-    a.max_sweeps = ctx->opt.mr_max_sweeps > 0 ? ctx->opt.mr_max_sweeps : 2;
+    // paths inside a tile are longer; with 8 the large image takes 16400 us
+    // with two, with 4 16384^2 1640 us with one).
+    a.max_sweeps = ctx->opt.mr_max_sweeps > 0 ? ctx->opt.mr_max_sweeps : 4;
     a.seed_sweeps = ctx->opt.mr_seed_sweeps > 0 ? ctx->opt.mr_seed_sweeps : (g.conn == 8 ? 1 : 2);
     a.seed_only = seed_only ? 1u : 0u;
     a.seed_strip = (uint32_t)ctx->opt.mr_seed_strip;

@@ -509,19 +509,21 @@ __device__ void fold_halo(WaveLds& L, uint64_t& rows, uint64_t& cols) {
 // not cover the wait.  So the forward and the backward scan of an axis run
 // together, in four passes of one 16-wide chunk each: the forward scan takes
 // chunks 0, 1, 2, 3, the backward scan 3, 2, 1, 0, never the same chunk in one
-// pass, and their independent steps fill each other's waits; a pass also pays
-// its LDS latency once for both (16384^2 with 4-connectivity 1728 -> 1707 us,
-// 4096^2 352 -> 342, 1500 x 1301 213 -> 205, 512^2 with 8 143.5 -> 140.5; the same
-// with the compiler's order of the steps and change tests: 1910, 398, 241, 160).
-// In place: from the third pass on each works on
-// what the other has raised.  Every value is a valid update of the ones it was
+// pass, and their independent steps fill each other's waits.  Each works on what
+// the other has raised.  Every value is a valid update of the ones it was
 // computed from and at least what either scan alone would give, and on a line
 // the limit is the larger of the two scans, so after a pair the line is stable.
 //
-// A chunk's results are written back if any of them changed.  A chunk whose
-// predecessors did not change since this scan last ran (`Dirty`), and that
-// follows no chunk this scan changed, is skipped; the chunk after a skipped one
-// reads its carried-in neighbour values from LDS.
+// The lane's whole line stays in registers over both scans (rows packed, 16
+// words and 16 of mask; columns a register a pixel): it is read from LDS once,
+// not once a scan, all of it before the first step with 4-connectivity, and by
+// chunk as scans need it with 8.  Of a chunk whose predecessors did not change
+// since a scan last ran (`Dirty`), and that follows no chunk the scan changed,
+// the scan is skipped; a chunk that no scan changed is not written back.
+//
+// Measured (us, one scan at a time from LDS -> pairs from LDS -> pairs in
+// registers): 16384^2 with 4-connectivity 1728, 1707, 1635; 4096^2 352, 342,
+// 331; with 8-connectivity, where only row scans pair, 16384^2 1551, 1537, 1530.
 constexpr int kChunk = 16;
 static_assert(T == 4 * kChunk, "four chunks per scan: with an even number no pass has both scans on one chunk");
 
@@ -567,7 +569,7 @@ __device__ __forceinline__ uint32_t or_diff(uint32_t a, uint32_t b, uint32_t d) 
         " src1_sel:BYTE_" #K "\n\t"                                                                     \
         "v_min_u32_sdwa %3, %1, %7 dst_sel:BYTE_" #K2 " dst_unused:UNUSED_PRESERVE src0_sel:DWORD"     \
         " src1_sel:BYTE_" #K2                                                                           \
-        : "=&v"(m_), "=&v"(m2_), "+v"(W), "+v"(W2)                                                      \
+        : "=&v"(m_), "=&v"(m2_), "+&v"(W), "+&v"(W2)                                                      \
         : "v"(PW), "v"(PW2), "v"(I), "v"(I2));                                                          \
   } while (0)
 
@@ -583,100 +585,111 @@ __device__ __forceinline__ uint32_t or_diff(uint32_t a, uint32_t b, uint32_t d) 
         " src1_sel:BYTE_" #K "\n\t"                                                                     \
         "v_min_u32_sdwa %3, %1, %5 dst_sel:BYTE_" #K2 " dst_unused:UNUSED_PRESERVE src0_sel:DWORD"     \
         " src1_sel:BYTE_" #K2                                                                           \
-        : "=&v"(m_), "=&v"(m2_), "+v"(W), "+v"(W2)                                                      \
+        : "=&v"(m_), "=&v"(m2_), "+&v"(W), "+&v"(W2)                                                      \
         : "v"(I), "v"(I2));                                                                             \
   } while (0)
 
-// A scan's state from one chunk to the next.
-struct Carry {
-  uint32_t prev = 0;    // the previous result: rows, the word holding it (byte 3 forward, byte 0 backward)
-  bool carried = true;  // prev is the previous chunk's result (the halo's zero before the first)
-  bool changed = false;  // the previous chunk changed
-};
-
-// One pass of the row scans: the forward scan (kF) on the chunk at column xf
-// and the backward scan (kB) on the one at xb.
-template <bool kF, bool kB>
-__device__ __forceinline__ void row_pass(WaveLds& L, int l, int xf, int xb, Carry& f, Carry& b, uint64_t& rows) {
-  uint32_t* jf = reinterpret_cast<uint32_t*>(&L.J[lidx(l, xf)]);
-  uint32_t* jb = reinterpret_cast<uint32_t*>(&L.J[lidx(l, xb)]);
-  const uint32_t* mf = reinterpret_cast<const uint32_t*>(&L.I[lidx(l, xf)]);
-  const uint32_t* mb = reinterpret_cast<const uint32_t*>(&L.I[lidx(l, xb)]);
-  uint32_t w[4], u[4], ow[4], ou[4], iw[4], iu[4];
-  if (kF && !f.carried) f.prev = jf[-1];
-  if (kB && !b.carried) b.prev = jb[4];
+// One pass of the row scans on the row in registers: the forward scan (kF) on
+// words [4 C, 4 C + 4), the backward scan (kB) on the mirrored chunk.  What
+// precedes a chunk is in the word beside it, whatever has been skipped.
+template <int C, bool kF, bool kB>
+__device__ __forceinline__ void row_pass(uint32_t (&w)[T / 4], const uint32_t (&m)[T / 4], uint32_t& df, uint32_t& db) {
+  const uint32_t zero = 0u;  // before the first pixel: the halo acts as zeros
 #pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    if (kF) ow[d] = w[d] = jf[d], iw[d] = mf[d];
-    if (kB) ou[d] = u[d] = jb[d], iu[d] = mb[d];
-  }
-  uint32_t df = 0, db = 0;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    const int e = 3 - d;
+  for (int k = 0; k < 4; ++k) {
+    const int d = 4 * C + k, e = T / 4 - 1 - d;
+    const uint32_t of = w[d], ob = w[e];
+    const uint32_t pf = d > 0 ? w[d > 0 ? d - 1 : 0] : zero, pb = d > 0 ? w[d > 0 ? e + 1 : e] : zero;
     if (kF && kB) {
-      MR_HSTEP2(w[d], f.prev, iw[d], 0, 3, u[e], b.prev, iu[e], 3, 0);
-      MR_HSTEP1(w[d], iw[d], 1, 0, u[e], iu[e], 2, 3);
-      MR_HSTEP1(w[d], iw[d], 2, 1, u[e], iu[e], 1, 2);
-      MR_HSTEP1(w[d], iw[d], 3, 2, u[e], iu[e], 0, 1);
+      MR_HSTEP2(w[d], pf, m[d], 0, 3, w[e], pb, m[e], 3, 0);
+      MR_HSTEP1(w[d], m[d], 1, 0, w[e], m[e], 2, 3);
+      MR_HSTEP1(w[d], m[d], 2, 1, w[e], m[e], 1, 2);
+      MR_HSTEP1(w[d], m[d], 3, 2, w[e], m[e], 0, 1);
     } else if (kF) {
-      MR_HSTEP(w[d], f.prev, iw[d], 0, 3);
-      MR_HSTEP(w[d], w[d], iw[d], 1, 0);
-      MR_HSTEP(w[d], w[d], iw[d], 2, 1);
-      MR_HSTEP(w[d], w[d], iw[d], 3, 2);
+      MR_HSTEP(w[d], pf, m[d], 0, 3);
+      MR_HSTEP(w[d], w[d], m[d], 1, 0);
+      MR_HSTEP(w[d], w[d], m[d], 2, 1);
+      MR_HSTEP(w[d], w[d], m[d], 3, 2);
     } else {
-      MR_HSTEP(u[e], b.prev, iu[e], 3, 0);
-      MR_HSTEP(u[e], u[e], iu[e], 2, 3);
-      MR_HSTEP(u[e], u[e], iu[e], 1, 2);
-      MR_HSTEP(u[e], u[e], iu[e], 0, 1);
+      MR_HSTEP(w[e], pb, m[e], 3, 0);
+      MR_HSTEP(w[e], w[e], m[e], 2, 3);
+      MR_HSTEP(w[e], w[e], m[e], 1, 2);
+      MR_HSTEP(w[e], w[e], m[e], 0, 1);
     }
-    if (kF) df = or_diff(ow[d], w[d], df), f.prev = w[d];
-    if (kB) db = or_diff(ou[e], u[e], db), b.prev = u[e];
-  }
-  if (kF) {
-    const uint64_t r = ballot(df != 0u);
-    f.carried = true;
-    f.changed = r != 0ull;
-    if (f.changed) {  // a chunk that changed nothing is not written back
-#pragma unroll
-      for (int d = 0; d < 4; ++d) jf[d] = w[d];
-      rows |= r;
-    }
-  }
-  if (kB) {
-    const uint64_t r = ballot(db != 0u);
-    b.carried = true;
-    b.changed = r != 0ull;
-    if (b.changed) {
-#pragma unroll
-      for (int d = 0; d < 4; ++d) jb[d] = u[d];
-      rows |= r;
-    }
+    if (kF) df = or_diff(of, w[d], df);
+    if (kB) db = or_diff(ob, w[e], db);
   }
 }
 
-// Both row scans; returns the rows that changed.
+// The lane's row in registers, chunk by chunk as scans need them (bit c of
+// `have`); bit c of `changed`: to be written back.
+struct Row {
+  uint32_t w[T / 4], m[T / 4];
+  uint32_t have = 0u, changed = 0u;
+};
+
+template <int C>
+__device__ __forceinline__ void load_row_chunk(const uint32_t* jp, const uint32_t* ip, Row& r) {
+#pragma unroll
+  for (int d = 4 * C; d < 4 * C + 4; ++d) {
+    r.w[d] = jp[d];
+    r.m[d] = ip[d];
+  }
+}
+
+// A pass with its chunks' needs; returns the rows that changed.
+template <int C, bool kDirty>
+__device__ __forceinline__ uint64_t row_chunks(const uint32_t* jp, const uint32_t* ip, Row& r, uint64_t dirty, bool& f, bool& b) {
+  constexpr int cf = C, cb = T / kChunk - 1 - C;
+  uint32_t df = 0, db = 0;
+  if (!kDirty) {
+    row_pass<C, true, true>(r.w, r.m, df, db);
+  } else {
+    f = f || (dirty & chunk_preds(cf * kChunk, true)) != 0ull;
+    b = b || (dirty & chunk_preds(cb * kChunk, false)) != 0ull;
+    // The chunk, if the other scan has not loaded it, and the word before it.
+    if (f && !(r.have >> cf & 1u)) load_row_chunk<cf>(jp, ip, r);
+    if (b && !(r.have >> cb & 1u)) load_row_chunk<cb>(jp, ip, r);
+    r.have |= (f ? 1u << cf : 0u) | (b ? 1u << cb : 0u);
+    if (C > 0 && f && !(r.have >> (C > 0 ? cf - 1 : 0) & 1u)) r.w[C > 0 ? 4 * cf - 1 : 0] = jp[4 * cf - 1];
+    if (C > 0 && b && !(r.have >> (C > 0 ? cb + 1 : 0) & 1u)) r.w[C > 0 ? 4 * cb + 4 : 0] = jp[4 * cb + 4];
+    if (f && b)
+      row_pass<C, true, true>(r.w, r.m, df, db);
+    else if (f)
+      row_pass<C, true, false>(r.w, r.m, df, db);
+    else if (b)
+      row_pass<C, false, true>(r.w, r.m, df, db);
+  }
+  const uint64_t rf = ballot(df != 0u), rb = ballot(db != 0u);
+  f = rf != 0ull;
+  b = rb != 0ull;
+  r.changed |= (f ? 1u << cf : 0u) | (b ? 1u << cb : 0u);
+  return rf | rb;
+}
+
+// Both row scans (lane = row); returns the rows that changed.
 template <bool kDirty>
 __device__ __forceinline__ uint64_t row_pair(WaveLds& L, int l, uint64_t dirty) {
-  Carry f, b;
-  uint64_t rows = 0ull;
-#pragma unroll 1
+  uint32_t* jp = reinterpret_cast<uint32_t*>(&L.J[lidx(l, 0)]);
+  const uint32_t* ip = reinterpret_cast<const uint32_t*>(&L.I[lidx(l, 0)]);
+  Row r;
+  if (!kDirty) {
+    load_row_chunk<0>(jp, ip, r);
+    load_row_chunk<3>(jp, ip, r);
+    load_row_chunk<1>(jp, ip, r);
+    load_row_chunk<2>(jp, ip, r);
+  }
+  bool f = false, b = false;
+  uint64_t rows = row_chunks<0, kDirty>(jp, ip, r, dirty, f, b);
+  rows |= row_chunks<1, kDirty>(jp, ip, r, dirty, f, b);
+  rows |= row_chunks<2, kDirty>(jp, ip, r, dirty, f, b);
+  rows |= row_chunks<3, kDirty>(jp, ip, r, dirty, f, b);
+#pragma unroll
   for (int c = 0; c < T / kChunk; ++c) {
-    const int xf = c * kChunk, xb = T - kChunk - xf;
-    if (!kDirty) {
-      row_pass<true, true>(L, l, xf, xb, f, b, rows);
-      continue;
+    if (r.changed >> c & 1u) {  // a chunk that changed nothing is not written back
+#pragma unroll
+      for (int d = 4 * c; d < 4 * c + 4; ++d) jp[d] = r.w[d];
     }
-    const bool do_f = f.changed || (dirty & chunk_preds(xf, true)) != 0ull;
-    const bool do_b = b.changed || (dirty & chunk_preds(xb, false)) != 0ull;
-    if (!do_f) f.carried = f.changed = false;
-    if (!do_b) b.carried = b.changed = false;
-    if (do_f && do_b)
-      row_pass<true, true>(L, l, xf, xb, f, b, rows);
-    else if (do_f)
-      row_pass<true, false>(L, l, xf, xb, f, b, rows);
-    else if (do_b)
-      row_pass<false, true>(L, l, xf, xb, f, b, rows);
   }
   wave_sync();
   return rows;
@@ -766,95 +779,114 @@ __device__ __forceinline__ void column_step1(uint32_t& v, uint32_t& p, uint32_t&
 #undef MR_SHL
 #undef MR_MAX
 
+// Steps K .. 15 of chunk C of the forward scan (kF) and of the mirrored chunk of
+// the backward scan (kB), on the column v in registers.  pf, pb: the rows before
+// this one; of, ob: their old values.
 template <int CONN, int C, int K, bool kF, bool kB>
-__device__ __forceinline__ void column_steps(uint32_t (&vf)[kChunk], uint32_t (&vb)[kChunk], uint32_t& df, uint32_t& db,
-                                             const uint32_t (&ic)[T / 4], Carry& f, Carry& b, uint32_t of,
-                                             uint32_t ob) {
+__device__ __forceinline__ void column_steps(uint32_t (&v)[T], uint32_t& df, uint32_t& db, const uint32_t (&ic)[T / 4],
+                                             uint32_t pf, uint32_t pb, uint32_t of, uint32_t ob) {
   if constexpr (K < kChunk) {
     constexpr int sf = C * kChunk + K, sb = T - 1 - sf;  // this step's rows
     static_assert((sf & 3) + (sb & 3) == 3, "the backward scan's mask byte mirrors the forward scan's");
     if constexpr (kF && kB)
-      column_step2<CONN, (sf & 3)>(vf[K], f.prev, of, df, ic[sf / 4], vb[K], b.prev, ob, db, ic[sb / 4]);
+      column_step2<CONN, (sf & 3)>(v[sf], pf, of, df, ic[sf / 4], v[sb], pb, ob, db, ic[sb / 4]);
     else if constexpr (kF)
-      column_step1<(sf & 3)>(vf[K], f.prev, of, df, ic[sf / 4]);
+      column_step1<(sf & 3)>(v[sf], pf, of, df, ic[sf / 4]);
     else
-      column_step1<(sb & 3)>(vb[K], b.prev, ob, db, ic[sb / 4]);
-    column_steps<CONN, C, K + 1, kF, kB>(vf, vb, df, db, ic, f, b, of, ob);
+      column_step1<(sb & 3)>(v[sb], pb, ob, db, ic[sb / 4]);
+    column_steps<CONN, C, K + 1, kF, kB>(v, df, db, ic, pf, pb, of, ob);
   } else {
-    if constexpr (kF) df = or_diff(of, f.prev, df);
-    if constexpr (kB) db = or_diff(ob, b.prev, db);
+    if constexpr (kF) df = or_diff(of, pf, df);
+    if constexpr (kB) db = or_diff(ob, pb, db);
   }
 }
 
-// Pass C of the column scans: the forward scan (kF) on rows [16 C, 16 C + 16)
-// and the backward scan (kB) on the mirrored chunk.
+// The chunk's steps from the row before it on (the halo acts as zeros).
 template <int CONN, int C, bool kF, bool kB>
-__device__ __forceinline__ void column_pass(WaveLds& L, int l, const uint32_t (&ic)[T / 4], Carry& f, Carry& b, uint64_t& cols) {
-  constexpr int yf = C * kChunk, yb = T - 1 - yf;  // the scans' first rows
-  uint32_t vf[kChunk], vb[kChunk], df = 0, db = 0;
-  if (kF && !f.carried) f.prev = L.J[lidx(yf - 1, l)];
-  if (kB && !b.carried) b.prev = L.J[lidx(yb + 1, l)];
-#pragma unroll
-  for (int k = 0; k < kChunk; ++k) {
-    if (kF) vf[k] = L.J[lidx(yf + k, l)];
-    if (kB) vb[k] = L.J[lidx(yb - k, l)];
-  }
-  column_steps<CONN, C, 0, kF, kB>(vf, vb, df, db, ic, f, b, f.prev, b.prev);
-  if (kF) {
-    const uint64_t c = ballot(df != 0u);
-    f.carried = true;
-    f.changed = c != 0ull;
-    if (f.changed) {  // a chunk that changed nothing is not written back
-#pragma unroll
-      for (int k = 0; k < kChunk; ++k) L.J[lidx(yf + k, l)] = (uint8_t)vf[k];
-      cols |= c;
-    }
-  }
-  if (kB) {
-    const uint64_t c = ballot(db != 0u);
-    b.carried = true;
-    b.changed = c != 0ull;
-    if (b.changed) {
-#pragma unroll
-      for (int k = 0; k < kChunk; ++k) L.J[lidx(yb - k, l)] = (uint8_t)vb[k];
-      cols |= c;
-    }
-  }
-  asm volatile("" ::: "memory");  // keep passes apart: bounded register use
+__device__ __forceinline__ void column_pass(uint32_t (&v)[T], uint32_t& df, uint32_t& db, const uint32_t (&ic)[T / 4]) {
+  const uint32_t pf = C > 0 ? v[C > 0 ? C * kChunk - 1 : 0] : 0u, pb = C > 0 ? v[C > 0 ? T - C * kChunk : 0] : 0u;
+  column_steps<CONN, C, 0, kF, kB>(v, df, db, ic, pf, pb, pf, pb);
 }
 
-// Both column scans; returns the columns that changed.  With 8-connectivity one
-// after the other: together they would leave the diagonal offers of each
-// other's last two passes for another pair (16384^2: 1618 us, one after the other
-// 1537).
-template <int CONN, bool kDirty, int C, bool kF, bool kB>
-__device__ __forceinline__ void column_chunk(WaveLds& L, int l, const uint32_t (&ic)[T / 4], Carry& f, Carry& b, Dirty& dm,
-                                             uint64_t& cols) {
-  if constexpr (kDirty) {
-    static_assert(kF != kB, "dirty chunks are tracked by scan");
-    constexpr int y0 = kF ? C * kChunk : T - kChunk - C * kChunk;
-    Carry& c = kF ? f : b;
-    if (!c.changed && ((kF ? dm.r_cf : dm.r_cb) & chunk_preds(y0, kF)) == 0ull) {
-      c.carried = false;
-      return;
-    }
-    column_pass<CONN, C, kF, kB>(L, l, ic, f, b, cols);
-    if (c.changed) (kF ? dm.r_cb : dm.r_cf) |= 0xFFFFull << y0;
-  } else {
-    column_pass<CONN, C, kF, kB>(L, l, ic, f, b, cols);
+template <int C>
+__device__ __forceinline__ void store_chunk(WaveLds& L, int l, const uint32_t (&v)[T]) {
+#pragma unroll
+  for (int k = C * kChunk; k < (C + 1) * kChunk; ++k) L.J[lidx(k, l)] = (uint8_t)v[k];
+}
+
+template <int C>
+__device__ __forceinline__ void load_chunk(const WaveLds& L, int l, uint32_t (&v)[T]) {
+#pragma unroll
+  for (int k = C * kChunk; k < (C + 1) * kChunk; ++k) v[k] = L.J[lidx(k, l)];
+}
+
+// A chunk of one scan, if it needs it (8-connectivity).
+template <int C, bool kF>
+__device__ __forceinline__ void column_chunk(const WaveLds& L, int l, uint32_t (&v)[T], const uint32_t (&ic)[T / 4],
+                                             Dirty& dm, bool& carry, uint64_t& cols, uint32_t& have, uint32_t& chunks) {
+  constexpr int kPos = kF ? C : T / kChunk - 1 - C, kPrev = C == 0 ? kPos : kF ? kPos - 1 : kPos + 1;
+  if (!carry && ((kF ? dm.r_cf : dm.r_cb) & chunk_preds(kPos * kChunk, kF)) == 0ull) return;
+  if (!(have >> kPos & 1u)) load_chunk<kPos>(L, l, v);
+  if (C > 0 && !(have >> kPrev & 1u)) {  // the row before the chunk
+    constexpr int r = kF ? kPos * kChunk - (C > 0 ? 1 : 0) : kPos * kChunk + kChunk - (C > 0 ? 0 : 1);
+    v[r] = L.J[lidx(r, l)];
+  }
+  have |= 1u << kPos;
+  uint32_t d = 0;
+  column_pass<8, C, kF, !kF>(v, d, d, ic);
+  const uint64_t c = ballot(d != 0u);
+  carry = c != 0ull;
+  if (carry) {
+    cols |= c;
+    chunks |= 1u << kPos;
+    (kF ? dm.r_cb : dm.r_cf) |= 0xFFFFull << (kPos * kChunk);
   }
 }
 
-template <int CONN, bool kDirty, bool kF, bool kB>
-__device__ __forceinline__ uint64_t column_scan(WaveLds& L, int l, const uint32_t (&ic)[T / 4], Dirty& dm) {
-  Carry f, b;
+// Both column scans (lane = column); returns the columns that changed.  With
+// 8-connectivity one after the other: together they would leave the diagonal
+// offers of each other's last two passes for another pair (16384^2: 1618 us,
+// one after the other 1537).
+template <int CONN, bool kDirty>
+__device__ __forceinline__ uint64_t column_pair(WaveLds& L, int l, const uint32_t (&ic)[T / 4], Dirty& dm) {
+  uint32_t v[T];
   uint64_t cols = 0ull;
-  column_chunk<CONN, kDirty, 0, kF, kB>(L, l, ic, f, b, dm, cols);
-  column_chunk<CONN, kDirty, 1, kF, kB>(L, l, ic, f, b, dm, cols);
-  column_chunk<CONN, kDirty, 2, kF, kB>(L, l, ic, f, b, dm, cols);
-  column_chunk<CONN, kDirty, 3, kF, kB>(L, l, ic, f, b, dm, cols);
-  if constexpr (kF != kB) (kF ? dm.r_cf : dm.r_cb) = 0ull;
-  else dm.r_cf = dm.r_cb = 0ull;
+  uint32_t chunks = 0u;
+  if constexpr (kDirty) {
+    bool carry = false;
+    uint32_t have = 0u;
+    column_chunk<0, true>(L, l, v, ic, dm, carry, cols, have, chunks);
+    column_chunk<1, true>(L, l, v, ic, dm, carry, cols, have, chunks);
+    column_chunk<2, true>(L, l, v, ic, dm, carry, cols, have, chunks);
+    column_chunk<3, true>(L, l, v, ic, dm, carry, cols, have, chunks);
+    dm.r_cf = 0ull;
+    carry = false;
+    column_chunk<0, false>(L, l, v, ic, dm, carry, cols, have, chunks);
+    column_chunk<1, false>(L, l, v, ic, dm, carry, cols, have, chunks);
+    column_chunk<2, false>(L, l, v, ic, dm, carry, cols, have, chunks);
+    column_chunk<3, false>(L, l, v, ic, dm, carry, cols, have, chunks);
+    dm.r_cb = 0ull;
+  } else {
+    load_chunk<0>(L, l, v);
+    load_chunk<3>(L, l, v);
+    load_chunk<1>(L, l, v);
+    load_chunk<2>(L, l, v);
+    uint32_t d[T / kChunk] = {0u, 0u, 0u, 0u};
+    column_pass<CONN, 0, true, true>(v, d[0], d[3], ic);
+    column_pass<CONN, 1, true, true>(v, d[1], d[2], ic);
+    column_pass<CONN, 2, true, true>(v, d[2], d[1], ic);
+    column_pass<CONN, 3, true, true>(v, d[3], d[0], ic);
+#pragma unroll
+    for (int c = 0; c < T / kChunk; ++c) {
+      const uint64_t b = ballot(d[c] != 0u);
+      cols |= b;
+      chunks |= b ? 1u << c : 0u;
+    }
+  }
+  if (chunks & 1u) store_chunk<0>(L, l, v);
+  if (chunks & 2u) store_chunk<1>(L, l, v);
+  if (chunks & 4u) store_chunk<2>(L, l, v);
+  if (chunks & 8u) store_chunk<3>(L, l, v);
   wave_sync();
   return cols;
 }
@@ -906,13 +938,7 @@ __device__ bool sweep_tile(WaveLds& L, int max_it, uint32_t& iters, bool& change
         rose = r != 0ull;
       }
     } else if (!kDirty || (dm.r_cf | dm.r_cb)) {
-      uint64_t c = 0ull;
-      if constexpr (kDirty) {
-        if (dm.r_cf) c |= column_scan<CONN, true, true, false>(L, l, ic, dm);
-        if (dm.r_cb) c |= column_scan<CONN, true, false, true>(L, l, ic, dm);
-      } else {
-        c = column_scan<CONN, false, true, true>(L, l, ic, dm);
-      }
+      const uint64_t c = column_pair<CONN, kDirty>(L, l, ic, dm);
       dm.c_r |= c;
       rose = c != 0ull;
     }
@@ -1170,7 +1196,7 @@ __device__ __forceinline__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStag
 // image.  The flags and the counts must be zero when the kernel starts.
 // WPB waves per workgroup.
 template <int CONN, int WPB>
-__global__ __launch_bounds__(64 * WPB, 16 / WPB) void k_propagate(MrArgs a) {
+__global__ __launch_bounds__(64 * WPB, 4) void k_propagate(MrArgs a) {
   __shared__ WaveLds lds[WPB];
   __shared__ uint32_t stage_mem[WPB][kStageCap];
   __shared__ uint32_t cnt[kShards];
