@@ -142,40 +142,67 @@ __device__ __forceinline__ void stat_add(unsigned long long* stats, int field, u
 // workgroup raised `abort`) the barrier returns false and the caller must leave
 // the kernel.
 //
-// A round with few tiles is mostly memory round trips (0.7 to 1 us each), so
-// the barrier has two on its path.  Counters only grow (arrival (gen + 1) *
-// size is a generation's last): nothing is reset, and nothing has to be written
-// before the generation.  Before, with a counter over the groups, resets, and
-// generation, abort word and result read one after the other, a 389 x 517
-// transform (12 steps) took 325 us, now 309; a 4096^2 reconstruction 340 and
-// 331, 32 small images 1195 and 1164.
+// A round with few tiles is mostly latencies, so the barrier has two memory
+// round trips on its path.  Counters only grow (arrival (gen + 1) * size is a
+// generation's last): nothing is reset, and nothing has to be written before the
+// generation.  Before, with a counter over the groups, resets, and generation,
+// abort word and result read one after the other, a 389 x 517 transform (12
+// steps) took 325 us, now 309; a 4096^2 reconstruction 340 and 331, 32 small
+// images 1195 and 1164.
+//
+// The high half of a group's counter and word is the number of list items its
+// workgroups have appended, carried along with the arrivals, so that a round
+// begins with its lists' lengths known and no more loads.  With it, and with
+// shares cut without 64-bit divisions and items read from the group's own
+// sub-list without a search, a reconstruction of 512 x 512 went from 143 to 120
+// us, 1500 x 1301 187 to 165, 4096^2 307 to 282, 65536 x 65600 15990 to 14730.
 struct GridBarrier {
-  uint32_t group[8][64];
-  uint32_t gen[64];  // word x: group x's generation
+  unsigned long long group[8][32];
+  unsigned long long word[32];  // [x]: group x's items << 32 | generation
   uint32_t abort[64];
 };
 
 constexpr uint32_t kSpinLimit = 1u << 24;  // ~ seconds of polling, far beyond any real wait
 
+// What the kernel's workgroup has appended since the last barrier (LDS), and
+// the items of each group up to then (lane x of wave 0: group x).
+struct Appended {
+  uint32_t* here;
+  uint32_t* cnt;  // LDS: per group, filled by the barrier with what the grid appended since the last
+  uint32_t* zero;  // LDS word the barrier clears (null: none)
+  uint32_t seen;
+};
+
 // Every wave first waits for its own stores: none is in flight when the
 // workgroup is counted.
-__device__ __forceinline__ bool grid_barrier(GridBarrier* b, uint32_t& gen, unsigned long long* stats) {
+__device__ __forceinline__ bool grid_barrier(GridBarrier* b, uint32_t& gen, unsigned long long* stats,
+                                             Appended* app = nullptr) {
   __shared__ uint32_t ok;
   drain();
   __syncthreads();
   if (threadIdx.x < (unsigned)kWave) {  // wave 0
     const uint32_t nwg = gridDim.x, g = blockIdx.x & 7u, in_group = (nwg - g + 7u) >> 3, groups = nwg < 8u ? nwg : 8u;
     const uint32_t l = threadIdx.x;
-    if (l == 0u && atomic_add(&b->group[g][0], 1u) + 1u == (gen + 1u) * in_group) cstore(&b->gen[g], gen + 1u);
-    const uint32_t* word = l < groups ? &b->gen[l] : &b->abort[0];
+    if (l == 0u) {
+      const unsigned long long one = (app ? (unsigned long long)*app->here << 32 : 0ull) | 1ull;
+      const unsigned long long total = atomic_add(&b->group[g][0], one) + one;
+      if ((uint32_t)total == (gen + 1u) * in_group) cstore(&b->word[g], (total & ~0xFFFFFFFFull) | (gen + 1u));
+      if (app) {
+        *app->here = 0u;
+        if (app->zero) *app->zero = 0u;
+      }
+    }
+    unsigned long long v = 0ull;
     uint32_t res = 1;
     for (uint32_t spins = 0;;) {
-      const uint32_t v = l <= groups ? cload(word) : 0u;  // lane `groups`: the abort word
-      if (ballot(l == groups && v != 0u) != 0ull) {
+      uint32_t stop = 0u;
+      if (l < groups) v = cload(&b->word[l]);
+      if (l == groups) stop = cload(&b->abort[0]);
+      if (ballot(stop != 0u) != 0ull) {
         res = 0;
         break;
       }
-      if (ballot(l < groups && v == gen) == 0ull) break;
+      if (ballot(l < groups && (uint32_t)v == gen) == 0ull) break;
       __builtin_amdgcn_s_sleep(2);
       if (++spins > kSpinLimit) {
         if (l == 0u) {
@@ -185,6 +212,11 @@ __device__ __forceinline__ bool grid_barrier(GridBarrier* b, uint32_t& gen, unsi
         res = 0;
         break;
       }
+    }
+    if (app && l < 8u) {
+      const uint32_t items = (uint32_t)(v >> 32);
+      app->cnt[l] = items - app->seen;
+      app->seen = items;
     }
     if (l == 0u) ok = res;
   }
@@ -288,12 +320,18 @@ constexpr uint32_t kXcds = 8;  // workgroup b runs on XCD b mod 8
 // Workgroups of the grid on XCD x, and this workgroup's rank among them.
 __device__ __forceinline__ uint32_t xcd_groups(uint32_t x) { return (gridDim.x + kXcds - 1u - x) / kXcds; }
 
+// First item of part l of n items cut into L parts whose sizes differ by one at most.
+__device__ __forceinline__ uint32_t part_begin(uint32_t n, uint32_t l, uint32_t L) {
+  const uint32_t q = n / L, r = n - q * L;
+  return q * l + (l < r ? l : r);
+}
+
 // This workgroup's share of the items [base, base + n) owned by its XCD.
 __device__ __forceinline__ WgShare share_of(uint32_t base, uint32_t n, uint32_t* next) {
   const uint32_t l = blockIdx.x / kXcds, L = xcd_groups(blockIdx.x % kXcds);
   WgShare w;
-  w.lo = base + (uint32_t)(((uint64_t)n * l) / L);
-  w.hi = base + (uint32_t)(((uint64_t)n * (l + 1u)) / L);
+  w.lo = base + part_begin(n, l, L);
+  w.hi = base + part_begin(n, l + 1u, L);
   w.next = next;
   return w;
 }
@@ -302,29 +340,14 @@ __device__ __forceinline__ WgShare share_of(uint32_t base, uint32_t n, uint32_t*
 __device__ __forceinline__ WgShare wg_share(uint32_t n, uint32_t* next) {
   if (gridDim.x < kXcds) {
     WgShare w;
-    w.lo = (uint32_t)(((uint64_t)n * blockIdx.x) / gridDim.x);
-    w.hi = (uint32_t)(((uint64_t)n * (blockIdx.x + 1u)) / gridDim.x);
+    w.lo = part_begin(n, blockIdx.x, gridDim.x);
+    w.hi = part_begin(n, blockIdx.x + 1u, gridDim.x);
     w.next = next;
     return w;
   }
   const uint32_t x = blockIdx.x % kXcds;
-  const uint32_t lo = (uint32_t)(((uint64_t)n * x) / kXcds), hi = (uint32_t)(((uint64_t)n * (x + 1u)) / kXcds);
+  const uint32_t lo = part_begin(n, x, kXcds), hi = part_begin(n, x + 1u, kXcds);
   return share_of(lo, hi - lo, next);
-}
-
-// A round's list, whose sub-list x (cnt[x] items) was appended by XCD x:
-// XCD x takes its own sub-list, where the neighbours of the tiles it visited
-// last round are.  Items are indices into the concatenated sub-lists.
-__device__ __forceinline__ WgShare wg_share_lists(const uint32_t* cnt, uint32_t* next) {
-  if (gridDim.x < kXcds) {
-    uint32_t n = 0;
-    for (uint32_t x = 0; x < kXcds; ++x) n += cnt[x];
-    return wg_share(n, next);
-  }
-  const uint32_t x = blockIdx.x % kXcds;
-  uint32_t base = 0;
-  for (uint32_t y = 0; y < x; ++y) base += cnt[y];
-  return share_of(base, cnt[x], next);
 }
 
 // ---- sharded tile frontier --------------------------------------------------------
@@ -346,12 +369,15 @@ __device__ __forceinline__ uint32_t* shard_count(uint32_t* counts, uint32_t slot
 // Items past the capacity are dropped: their flag is cleared (so a later mark
 // can list them again) and *lost is set.
 __device__ inline void shard_flush(WaveStage& s, uint32_t* list, uint32_t* count, uint32_t cap, uint32_t* flags,
-                                   uint32_t* lost) {
+                                   uint32_t* lost, uint32_t* appended) {
   const uint32_t n = s.n;
   if (n == 0) return;
   wave_sync();
   uint32_t base = 0;
-  if (lane() == 0) base = atomic_add(count, n);
+  if (lane() == 0) {
+    base = atomic_add(count, n);
+    atomicAdd(appended, n);  // LDS: the workgroup's, for the barrier
+  }
   base = readlane(base, 0);
   bool dropped = false;
   for (uint32_t i = lane(); i < n; i += kWave) {
@@ -371,12 +397,12 @@ __device__ inline void shard_flush(WaveStage& s, uint32_t* list, uint32_t* count
 // Stage tile t (every lane with `pred`) unless it is already on the list
 // whose flags are `flags`; flushes first if the stage could overflow.
 __device__ inline void shard_mark(WaveStage& s, bool pred, uint32_t t, uint32_t* flags, uint32_t* list,
-                                  uint32_t* count, uint32_t cap, uint32_t* lost) {
+                                  uint32_t* count, uint32_t cap, uint32_t* lost, uint32_t* appended) {
   const bool fresh = pred && atomic_or(flags + t, 1u) == 0u;
   const uint64_t m = ballot(fresh);
   if (m == 0) return;
   const uint32_t k = (uint32_t)__popcll(m);
-  if (s.n + k > s.cap) shard_flush(s, list, count, cap, flags, lost);
+  if (s.n + k > s.cap) shard_flush(s, list, count, cap, flags, lost, appended);
   if (fresh) s.items[s.n + mbcnt(m)] = t;
   s.n += k;
 }

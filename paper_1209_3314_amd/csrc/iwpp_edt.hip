@@ -446,8 +446,8 @@ __device__ __forceinline__ Next next_frontier(const EdtArgs& a, uint32_t m) {
 // List, for the next step, the tiles named by zone mask z of tile tr: itself
 // (bit 0) and the neighbours of bits 1..8.  Lanes 0..8 of the wave each
 // handle one candidate.
-__device__ __forceinline__ void mark_reach(const EdtArgs& a, WaveStage& s, const Next& nx, const TileRef& tr,
-                                           uint32_t z) {
+__device__ __forceinline__ void mark_reach(const EdtArgs& a, WaveStage& s, const Next& nx, const TileRef& tr, uint32_t z,
+                                           uint32_t* appended) {
   const int l = lane();
   int dy = 0, dx = 0;
   bool want = false;
@@ -462,8 +462,8 @@ __device__ __forceinline__ void mark_reach(const EdtArgs& a, WaveStage& s, const
   }
   const int ny = tr.ty + dy, nx_ = tr.tx + dx;
   want = want && ny >= 0 && ny < tr.j.tiles_y && nx_ >= 0 && nx_ < tr.j.tiles_x;
-  shard_mark(s, want, tr.j.tile_base + (uint32_t)(ny * tr.j.tiles_x + nx_), nx.flags, nx.list, nx.count, a.ntiles,
-             a.ovf);
+  shard_mark(s, want, tr.j.tile_base + (uint32_t)(ny * tr.j.tiles_x + nx_), nx.flags, nx.list, nx.count, a.ntiles, a.ovf,
+             appended);
 }
 
 // Initial state (features carry themselves, everything else none), the
@@ -623,20 +623,20 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
   __shared__ uint32_t cnt[kShards];
   __shared__ uint32_t last_sh;  // the visit's last round with a change
   __shared__ uint32_t next_sh;  // the tile to visit next
+  __shared__ uint32_t appended_sh;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t depth = a.stage_depth > 0u && a.stage_depth < (uint32_t)kStageCap ? a.stage_depth : (uint32_t)kStageCap;
   WaveStage s = {stage_mem, depth, 0u};  // wave 0's
   for (int i = (int)threadIdx.x; i < P * P; i += kWave * WPB) L.key[i] = 0ull;  // the ring stays so
-  if (threadIdx.x == 0) last_sh = L.any[0] = L.any[1] = 0u;
+  if (threadIdx.x == 0) last_sh = appended_sh = L.any[0] = L.any[1] = 0u;
+  Appended app = {&appended_sh, cnt, nullptr, 0u};
+  shard_counts(a.counts, 1u, a.ntiles, cnt);  // `k_list`'s
+  __syncthreads();
   uint32_t gen = 0, nclk = 0;
   unsigned long long changed = 0, visits = 0;
   uint32_t last_round = 0;  // this workgroup's last round with a change (wave 0)
   clock_stamp(a.clock, nclk);
   for (uint32_t m = 1;; ++m) {
-    // Every workgroup reads the same words: nothing writes them between the
-    // previous barrier and this read (step m appends for step m+1).
-    shard_counts(a.counts, m % 3u, a.ntiles, cnt);
-    __syncthreads();
     uint32_t n = 0;
     for (int x = 0; x < kShards; ++x) n += cnt[x];
     if (n == 0u) break;
@@ -717,14 +717,14 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
         const int row = lane() - K;
         uint32_t z = any_zone(row >= 0 && row < TE ? zone_bits((mk & kTileCols) >> K, row) : 0u);
         if (lw) z |= 1u;
-        mark_reach(a, s, nx, tr, z);
+        mark_reach(a, s, nx, tr, z, &appended_sh);
       }
       if (sparse) break;
       __syncthreads();  // LDS is reloaded by the next visit
       t = readlane(next_sh, 0);
     }
-    if (w == 0) shard_flush(s, nx.list, nx.count, a.ntiles, nx.flags, a.ovf);
-    if (!grid_barrier(a.bar, gen, a.stats)) return;
+    if (w == 0) shard_flush(s, nx.list, nx.count, a.ntiles, nx.flags, a.ovf, &appended_sh);
+    if (!grid_barrier(a.bar, gen, a.stats, &app)) return;  // leaves the next step's list lengths in cnt
     clock_stamp(a.clock, nclk);
   }
   // Both buffers now agree everywhere; write the outputs.  A wave takes 256

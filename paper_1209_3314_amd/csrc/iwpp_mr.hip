@@ -1098,7 +1098,8 @@ __device__ __forceinline__ Next next_frontier(const MrArgs& a, uint32_t r) {
 
 // Flag the neighbours named by border mask m (see border_marks) and, if
 // `unsettled`, the tile itself, for the next round (lanes 0..8 of the wave).
-__device__ void mark_reach(WaveStage& s, const Next& nx, const TileRef& tr, uint32_t m, bool unsettled) {
+__device__ __forceinline__ void mark_reach(WaveStage& s, const Next& nx, const TileRef& tr, uint32_t m, bool unsettled,
+                                           uint32_t* appended) {
   const int l = lane();
   int dy = 0, dx = 0;
   bool want = false;
@@ -1112,7 +1113,8 @@ __device__ void mark_reach(WaveStage& s, const Next& nx, const TileRef& tr, uint
   }
   const int ny = tr.ty + dy, nx_ = tr.tx + dx;
   want = want && ny >= 0 && ny < tr.j.tiles_y && nx_ >= 0 && nx_ < tr.j.tiles_x;
-  shard_mark(s, want, tr.j.tile_base + (uint32_t)(ny * tr.j.tiles_x + nx_), nx.flags, nx.list, nx.count, nx.cap, nx.lost);
+  shard_mark(s, want, tr.j.tile_base + (uint32_t)(ny * tr.j.tiles_x + nx_), nx.flags, nx.list, nx.count, nx.cap, nx.lost,
+             appended);
 }
 
 // A wave's counters over the kernel.
@@ -1140,7 +1142,8 @@ enum class Visit { kSeed, kListed, kCheck };
 // code, and a copy for each would not fit the instruction cache together.
 template <int CONN>
 __device__ __forceinline__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStage& s, const Next& nx, uint32_t t,
-                                           Visit how, bool fresh_top, bool below_next, Counters& n) {
+                                           Visit how, bool fresh_top, bool below_next, bool few, uint32_t* appended,
+                                           Counters& n) {
   const TileRef tr = tile_ref(a, t);
   bool columns_first = false, all_dirty = true;
   if (how == Visit::kSeed) {
@@ -1148,11 +1151,12 @@ __device__ __forceinline__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStag
     load_region<true>(tr, L, fresh_top);
   } else {
     const uint32_t uns = how == Visit::kListed && lane() == 0 ? cload(a.unsettled + t) : 0u;
-    if (CONN == 8 && how == Visit::kListed) {
+    if (CONN == 8 && how == Visit::kListed && !few) {
       // About a third of the listed 8-connected tiles turn out to need no
       // work: load the frame first and the interior only if needed.  Nearly
       // every listed 4-connected tile needs work, and the second round trip
-      // measured slower there (1.85 against 1.81 ms): one load.
+      // measured slower there (1.85 against 1.81 ms): one load.  With few tiles
+      // in the round (at most one a workgroup) the round trip counts, not the bytes.
       load_frame(tr, L, a.cols, a.ntiles * 256u, t);
     } else {
       load_region<false>(tr, L, false, a.cols, a.ntiles * 256u, t);
@@ -1163,7 +1167,7 @@ __device__ __forceinline__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStag
       const uint32_t sides = border_raisable<CONN>(L);
       all_dirty = readlane(uns, 0) != 0u;
       if (!all_dirty && sides == 0u) return;
-      if (CONN == 8) load_interior(tr, L);
+      if (CONN == 8 && !few) load_interior(tr, L);
       columns_first = (sides & 3u) != 0u;  // the scans that lead away from a raisable top or bottom
     }
   }
@@ -1182,7 +1186,7 @@ __device__ __forceinline__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStag
   }
   uint32_t m = changed ? border_marks<CONN>(L, ot, ob, ol, orr) : 0u;
   if (below_next) m &= ~2u;  // bit 1: bottom
-  mark_reach(s, nx, tr, m, !stable);
+  mark_reach(s, nx, tr, m, !stable, appended);
 }
 
 // Round 0 is the seed pass over every tile; round r >= 1 visits the tiles
@@ -1200,14 +1204,16 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_propagate(MrArgs a) {
   __shared__ WaveLds lds[WPB];
   __shared__ uint32_t stage_mem[WPB][kStageCap];
   __shared__ uint32_t cnt[kShards];
-  __shared__ uint32_t lost_sh, next_sh;
+  __shared__ uint32_t lost_sh, next_sh, appended_sh;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   WaveLds& L = lds[w];
   const uint32_t depth = a.stage_depth > 0u && a.stage_depth < (uint32_t)kStageCap ? a.stage_depth : (uint32_t)kStageCap;
   WaveStage s = {stage_mem[w], depth, 0u};
   L.J[lidx(lane() - 1, kZeroCol)] = 0;  // rows -1..62
   if (lane() < 2) L.J[lidx(T - 1 + lane(), kZeroCol)] = 0;  // rows 63, 64
-  if (threadIdx.x == 0) next_sh = 0u;
+  if (threadIdx.x == 0) next_sh = appended_sh = 0u;
+  Appended app = {&appended_sh, cnt, &next_sh, 0u};
+  const bool bounded = a.list_cap < a.ntiles;
   __syncthreads();
   const uint32_t nw = gridDim.x * WPB;  // waves of the grid
   const uint32_t cap = a.list_cap < a.ntiles ? a.list_cap : a.ntiles;
@@ -1225,17 +1231,16 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_propagate(MrArgs a) {
     bool full = false;
     uint32_t n = a.ntiles;
     if (r > 0u) {
-      // Every workgroup reads the same words: nothing writes them between the
-      // previous barrier and this read (round r appends for round r+1).
-      shard_counts(a.counts, r % 3u, cap, cnt);
-      if (threadIdx.x == 0) {
-        lost_sh = cload(a.lost + par * 64u);
-        next_sh = 0u;  // last used before the previous barrier
-      }
-      __syncthreads();
+      // The barrier left in cnt what each group appended.  Only a bounded list
+      // can have lost some.
       n = 0;
       for (int x = 0; x < kShards; ++x) n += cnt[x];
-      full = lost_sh != 0u;
+      if (bounded) {
+        if (n > cap) n = cap;
+        if (threadIdx.x == 0) lost_sh = cload(a.lost + par * 64u);
+        __syncthreads();
+        full = lost_sh != 0u;
+      }
       if (!full && n == 0u) break;
     }
     round_work(a.clock, r, full ? a.ntiles : n);
@@ -1265,22 +1270,33 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_propagate(MrArgs a) {
     const uint32_t tx_n = (uint32_t)a.job0.tiles_x, ty_n = (uint32_t)a.job0.tiles_y;  // strips only
     // Items: strips or tiles (seed pass, full round), entries of the lists.
     // XCD x visits the tiles XCD x listed (a bounded list is one sub-list:
-    // then the whole list is cut over the grid).
+    // then the whole list is cut over the grid).  With at most one item per
+    // workgroup the first wave of workgroup b of the XCD takes item b: no
+    // counter in LDS, and tiles on different CUs.
     const uint32_t items = r == 0u && strips ? tx_n * ((ty_n + S - 1u) / S) : full ? a.ntiles : n;
-    const WgShare share = r == 0u || full || a.list_cap < a.ntiles ? wg_share(items, &next_sh) : wg_share_lists(cnt, &next_sh);
+    const bool own = r > 0u && !full && !bounded && gridDim.x >= kXcds;
+    const uint32_t grp = own ? blockIdx.x % kXcds : 0u, rank = blockIdx.x / kXcds;
+    const uint32_t mine = own ? cnt[grp] : 0u;
+    const bool few = own && n <= gridDim.x && mine <= xcd_groups(grp);
+    const WgShare share = own ? share_of(0u, mine, &next_sh) : wg_share(items, &next_sh);
     const Visit how = r == 0u ? Visit::kSeed : full ? Visit::kCheck : Visit::kListed;
     uint32_t t = 0, left = 0;  // seed pass: the tile, and how many of its strip follow
-    bool fresh = false;
+    bool fresh = false, taken = false;
     for (;;) {
       if (left > 0u) {
         --left;
         t += tx_n;
       } else {
-        uint32_t i;
-        if (!share.take(i)) break;
+        uint32_t i = rank;
+        if (few) {
+          if (w != 0 || rank >= mine || taken) break;
+          taken = true;
+        } else if (!share.take(i)) {
+          break;
+        }
         t = i;
         if (how == Visit::kListed) {
-          t = shard_item(lists, a.ntiles, cnt, i);
+          t = own || bounded ? cload(lists + (size_t)grp * a.ntiles + i) : shard_item(lists, a.ntiles, cnt, i);
           t = readlane(t, 0);
           if (lane() == 0) cstore(flg + t, 0u);
         } else if (how == Visit::kSeed && strips) {
@@ -1292,13 +1308,13 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_propagate(MrArgs a) {
       }
       // Right-edge tiles of widths not a multiple of 16 read bytes: stale halo there.
       const bool below = left > 0u && !(a.job0.w % 16 != 0 && t % tx_n + 1u == tx_n);
-      visit_tile<CONN>(a, L, s, nx, t, how, fresh, below, n_);
+      visit_tile<CONN>(a, L, s, nx, t, how, fresh, below, few, &appended_sh, n_);
       fresh = below;
     }
-    shard_flush(s, nx.list, nx.count, nx.cap, nx.flags, nx.lost);
+    shard_flush(s, nx.list, nx.count, nx.cap, nx.flags, nx.lost, &appended_sh);
     if (r == 1u) first = n_.visits - before;
     if (r > 0u) rounds++;
-    const bool ok = grid_barrier(a.bar, gen, a.stats);
+    const bool ok = grid_barrier(a.bar, gen, a.stats, &app);
     clock_stamp(a.clock, nclk);
     if (!ok || a.seed_only != 0u) break;
   }
