@@ -64,6 +64,24 @@ __device__ __forceinline__ int local_copy(int v) {
   asm volatile("" : "+v"(v));
   return v;
 }
+// The kernel's only argument, read again from where it lies (scalar loads).  In
+// a persistent kernel the fields would otherwise be read once, kept in scalar
+// registers over all loops and, past their number, in lanes of vector registers,
+// sixteen of them brought back for one that is needed (16384^2 reconstruction
+// 1507 us, read again in each visit 1487).
+template <typename Args>
+__device__ __forceinline__ Args kernel_args() {
+  static_assert(sizeof(Args) % 8 == 0, "read by 8-byte words");
+  typedef const __attribute__((address_space(4))) uint64_t* Words;
+  Words p = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  struct Raw {
+    uint64_t w[sizeof(Args) / 8];
+  } r;
+#pragma unroll
+  for (size_t k = 0; k < sizeof(Args) / 8; ++k) r.w[k] = p[k];
+  return __builtin_bit_cast(Args, r);
+}
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 __device__ __forceinline__ int mbcnt(uint64_t m) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -182,7 +200,7 @@ __device__ __forceinline__ bool grid_barrier(GridBarrier* b, uint32_t& gen, unsi
   __syncthreads();
   if (threadIdx.x < (unsigned)kWave) {  // wave 0
     const uint32_t nwg = gridDim.x, g = blockIdx.x & 7u, in_group = (nwg - g + 7u) >> 3, groups = nwg < 8u ? nwg : 8u;
-    const uint32_t l = threadIdx.x;
+    const uint32_t l = (uint32_t)local_copy((int)threadIdx.x);
     if (l == 0u) {
       const unsigned long long one = (app ? (unsigned long long)*app->here << 32 : 0ull) | 1ull;
       const unsigned long long total = atomic_add(&b->group[g][0], one) + one;
@@ -373,14 +391,15 @@ __device__ inline void shard_flush(WaveStage& s, uint32_t* list, uint32_t* count
   const uint32_t n = s.n;
   if (n == 0) return;
   wave_sync();
+  const uint32_t l = (uint32_t)local_copy(lane());
   uint32_t base = 0;
-  if (lane() == 0) {
+  if (l == 0u) {
     base = atomic_add(count, n);
     atomicAdd(appended, n);  // LDS: the workgroup's, for the barrier
   }
   base = readlane(base, 0);
   bool dropped = false;
-  for (uint32_t i = lane(); i < n; i += kWave) {
+  for (uint32_t i = l; i < n; i += kWave) {
     const uint32_t slot = base + i, item = s.items[i];
     if (slot < cap) {
       cstore(list + slot, item);
@@ -389,7 +408,7 @@ __device__ inline void shard_flush(WaveStage& s, uint32_t* list, uint32_t* count
       dropped = true;
     }
   }
-  if (ballot(dropped) && lane() == 0) cstore(lost, 1u);
+  if (ballot(dropped) && l == 0u) cstore(lost, 1u);
   wave_sync();
   s.n = 0;
 }

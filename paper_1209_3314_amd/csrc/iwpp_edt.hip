@@ -448,7 +448,7 @@ __device__ __forceinline__ Next next_frontier(const EdtArgs& a, uint32_t m) {
 // handle one candidate.
 __device__ __forceinline__ void mark_reach(const EdtArgs& a, WaveStage& s, const Next& nx, const TileRef& tr, uint32_t z,
                                            uint32_t* appended) {
-  const int l = lane();
+  const int l = local_copy(lane());
   int dy = 0, dx = 0;
   bool want = false;
   if (l == 0) {

@@ -88,7 +88,8 @@ struct TileRef {
 
 __device__ __forceinline__ TileRef tile_ref(const MrArgs& a, uint32_t t) {
   TileRef r;
-  r.j = uniform(a.njobs == 1u ? a.job0 : a.jobs[a.tile_job[t]]);
+  r.j = a.job0;
+  if (a.njobs != 1u) r.j = uniform(a.jobs[a.tile_job[t]]);
   const uint32_t lt = t - r.j.tile_base;
   r.ty = (int)(lt / (uint32_t)r.j.tiles_x);
   r.tx = (int)(lt - (uint32_t)r.ty * (uint32_t)r.j.tiles_x);
@@ -250,7 +251,7 @@ __device__ void load_region(const TileRef& tr, WaveLds& L, bool fresh_top = fals
       if (ry < kRows) {
 #pragma unroll
         for (int b = 0; b < 15; ++b) {
-          if (b >= nb) break;
+          if (b >= nb) continue;  // (a break would put the bytes in scratch)
           const int at = lidx(ry - 1, 16 * cp + b);
           L.J[at] = (uint8_t)(kSeed ? umin(bj[b], bi[b]) : bj[b]);
           L.I[at] = (uint8_t)bi[b];
@@ -392,7 +393,7 @@ __device__ void load_interior(const TileRef& tr, WaveLds& L) {
     if (ry < T - 1) {
 #pragma unroll
       for (int b = 0; b < 15; ++b) {
-        if (b >= nb) break;
+        if (b >= nb) continue;  // (a break would put the bytes in scratch)
         const int at = lidx(ry, 16 * cp + b);
         L.J[at] = (uint8_t)bj[b];
         L.I[at] = (uint8_t)bi[b];
@@ -958,9 +959,11 @@ __device__ __forceinline__ bool halo_raisable(const WaveLds& L, int qy, int qx, 
 
 // Neighbouring tiles that a change of this visit can raise, as a bit mask:
 // bit 0 top, 1 bottom, 2 left, 3 right, 4 top-left, 5 top-right,
-// 6 bottom-left, 7 bottom-right.  o* are the border values before the visit.
+// 6 bottom-left, 7 bottom-right.  `old`: the border values before the visit, a
+// byte each for top, bottom, left, right (one register over the sweep).
 template <int CONN>
-__device__ uint32_t border_marks(const WaveLds& L, uint32_t ot, uint32_t ob, uint32_t ol, uint32_t orr) {
+__device__ uint32_t border_marks(const WaveLds& L, uint32_t old) {
+  const uint32_t ot = old & 0xffu, ob = old >> 8 & 0xffu, ol = old >> 16 & 0xffu, orr = old >> 24;
   const int l = local_copy(lane());
   const uint32_t nt = L.J[lidx(0, l)], nb = L.J[lidx(T - 1, l)];
   const uint32_t nl = L.J[lidx(l, 0)], nr = L.J[lidx(l, T - 1)];
@@ -1100,7 +1103,7 @@ __device__ __forceinline__ Next next_frontier(const MrArgs& a, uint32_t r) {
 // `unsettled`, the tile itself, for the next round (lanes 0..8 of the wave).
 __device__ __forceinline__ void mark_reach(WaveStage& s, const Next& nx, const TileRef& tr, uint32_t m, bool unsettled,
                                            uint32_t* appended) {
-  const int l = lane();
+  const int l = local_copy(lane());
   int dy = 0, dx = 0;
   bool want = false;
   if (l < 8) {
@@ -1141,9 +1144,10 @@ enum class Visit { kSeed, kListed, kCheck };
 // One function for the three, called from one place: the sweep is some 40 KB of
 // code, and a copy for each would not fit the instruction cache together.
 template <int CONN>
-__device__ __forceinline__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStage& s, const Next& nx, uint32_t t,
+__device__ __forceinline__ void visit_tile(WaveLds& L, WaveStage& s, uint32_t round, uint32_t t,
                                            Visit how, bool fresh_top, bool below_next, bool few, uint32_t* appended,
                                            Counters& n) {
+  const MrArgs a = kernel_args<MrArgs>();
   const TileRef tr = tile_ref(a, t);
   bool columns_first = false, all_dirty = true;
   if (how == Visit::kSeed) {
@@ -1172,19 +1176,20 @@ __device__ __forceinline__ void visit_tile(const MrArgs& a, WaveLds& L, WaveStag
     }
   }
   const int l = local_copy(lane());
-  const uint32_t ot = L.J[lidx(0, l)], ob = L.J[lidx(T - 1, l)];
-  const uint32_t ol = L.J[lidx(l, 0)], orr = L.J[lidx(l, T - 1)];
+  const uint32_t old = L.J[lidx(0, l)] | (uint32_t)L.J[lidx(T - 1, l)] << 8 | (uint32_t)L.J[lidx(l, 0)] << 16 |
+                       (uint32_t)L.J[lidx(l, T - 1)] << 24;
   const bool seed = how == Visit::kSeed;
   bool changed;
   const bool stable =
       sweep_tile<CONN>(L, seed ? a.seed_sweeps : a.max_sweeps, n.iters, changed, all_dirty, columns_first);
   if (!seed) n.visits++;
+  const Next nx = next_frontier(a, round);
   if (lane() == 0) cstore(a.unsettled + t, stable ? 0u : 1u);
   if (changed || seed) {
     store_tile(tr, L);
     store_cols(a, t, L, seed);
   }
-  uint32_t m = changed ? border_marks<CONN>(L, ot, ob, ol, orr) : 0u;
+  uint32_t m = changed ? border_marks<CONN>(L, old) : 0u;
   if (below_next) m &= ~2u;  // bit 1: bottom
   mark_reach(s, nx, tr, m, !stable, appended);
 }
@@ -1263,7 +1268,6 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_propagate(MrArgs a) {
     // in round r-1, and are next appended to in round r+1, after this round's barrier).
     if (r > 0u && blockIdx.x == 0 && threadIdx.x < (unsigned)kShards)
       cstore(shard_count(a.counts, (r + 2u) % 3u, threadIdx.x), 0u);
-    const Next nx = next_frontier(a, r);
     const uint32_t before = n_.visits;
     const uint32_t* lists = a.lists + (size_t)par * kShards * a.ntiles;
     uint32_t* flg = a.flags + (size_t)par * a.ntiles;
@@ -1308,10 +1312,14 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_propagate(MrArgs a) {
       }
       // Right-edge tiles of widths not a multiple of 16 read bytes: stale halo there.
       const bool below = left > 0u && !(a.job0.w % 16 != 0 && t % tx_n + 1u == tx_n);
-      visit_tile<CONN>(a, L, s, nx, t, how, fresh, below, few, &appended_sh, n_);
+      visit_tile<CONN>(L, s, r, t, how, fresh, below, few, &appended_sh, n_);
       fresh = below;
     }
-    shard_flush(s, nx.list, nx.count, nx.cap, nx.flags, nx.lost, &appended_sh);
+    {
+      const MrArgs b = kernel_args<MrArgs>();
+      const Next nx = next_frontier(b, r);
+      shard_flush(s, nx.list, nx.count, nx.cap, nx.flags, nx.lost, &appended_sh);
+    }
     if (r == 1u) first = n_.visits - before;
     if (r > 0u) rounds++;
     const bool ok = grid_barrier(a.bar, gen, a.stats, &app);
