@@ -1194,6 +1194,20 @@ __device__ __forceinline__ void visit_tile(WaveLds& L, WaveStage& s, uint32_t ro
   mark_reach(s, nx, tr, m, !stable, appended);
 }
 
+// Tiles per strip of the seed pass.  A strip for every wave has no slack: with
+// 8-connectivity it pays only where the waves' strips come out even, at least
+// 95% of the waves' steps being tiles (us, strips against single tiles in row
+// order: 16384^2 1457, 1476; 12000^2 811, 844; 32768^2 6733, 6994).  Otherwise
+// and with 4-connectivity single tiles, of which a workgroup's faster waves take
+// more (65536 x 65600, where 4100 strips meet 4096 waves: 14360, 12887; 6000^2
+// 342, 331; 16384^2 with 4 1497, 1441; 24000^2 3683, 3532; but 12000^2 828, 844).
+__device__ __forceinline__ uint32_t auto_strip(const MrArgs& a, int conn, uint32_t nw) {
+  const uint32_t S = (a.ntiles + nw - 1u) / nw;
+  const uint32_t tx_n = (uint32_t)a.job0.tiles_x, ty_n = (uint32_t)a.job0.tiles_y;
+  const uint32_t nstrips = tx_n * ((ty_n + S - 1u) / S), passes = (nstrips + nw - 1u) / nw;
+  return conn == 8 && (uint64_t)a.ntiles * 20u >= (uint64_t)nw * S * passes * 19u ? S : 1u;
+}
+
 // Round 0 is the seed pass over every tile; round r >= 1 visits the tiles
 // listed in round r-1 and lists the tiles of round r+1 (parity (r+1)&1,
 // count slot (r+1)%3).  The list is split over kShards sub-lists, one per
@@ -1230,7 +1244,7 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_propagate(MrArgs a) {
   // tiles top to bottom, so the flood crosses the horizontal tile edges inside
   // the seed pass.  The strips are shared by the waves of each workgroup.
   const bool strips = a.njobs == 1u;
-  const uint32_t S = !strips ? 1u : a.seed_strip > 0u ? a.seed_strip : (a.ntiles + nw - 1u) / nw;
+  const uint32_t S = !strips ? 1u : a.seed_strip > 0u ? a.seed_strip : auto_strip(a, CONN, nw);
   for (uint32_t r = 0;; ++r) {
     const uint32_t par = r & 1u;
     bool full = false;
