@@ -860,17 +860,19 @@ hipError_t launch_persistent(const void* fn, uint32_t blocks, void** args, hipSt
   return hipLaunchCooperativeKernel(fn, dim3(blocks), dim3(threads), args, 0, s);
 }
 
-// Zero a range of 32-bit words with a kernel (no memset node, so the sequence
+// Zero two ranges of 32-bit words with one kernel (no memset node, so the sequence
 // can be captured into a graph).
-__global__ void k_zero(uint32_t* p, size_t n) {
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0u;
+__global__ void k_zero(uint32_t* p, size_t n, uint32_t* q, size_t m) {
+  const size_t i0 = blockIdx.x * (size_t)blockDim.x + threadIdx.x, step = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = i0; i < n; i += step) p[i] = 0u;
+  for (size_t i = i0; i < m; i += step) q[i] = 0u;
 }
 
-int zero_words(uint32_t* p, size_t nwords, hipStream_t stream) {
-  size_t blocks = (nwords + 255) / 256;
+int zero_words(uint32_t* p, size_t nwords, hipStream_t stream, uint32_t* q, size_t mwords) {
+  size_t blocks = ((nwords > mwords ? nwords : mwords) + 255) / 256;
   if (blocks > 1024) blocks = 1024;
   if (blocks == 0) return 0;
-  hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, stream, p, nwords);
+  hipLaunchKernelGGL(k_zero, dim3((unsigned)blocks), dim3(256), 0, stream, p, nwords, q, mwords);
   return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 

@@ -126,7 +126,7 @@ class Recorder {
 
 int mr_launch(const MrArgs& a, int conn, int persistent_blocks, hipStream_t stream, Recorder* rec, const char** err);
 int edt_launch(const EdtArgs& a, int conn, int persistent_blocks, hipStream_t stream, Recorder* rec, const char** err);
-int zero_words(uint32_t* p, size_t nwords, hipStream_t stream);
+int zero_words(uint32_t* p, size_t nwords, hipStream_t stream, uint32_t* q = nullptr, size_t mwords = 0);
 
 // Workgroups for a cooperative (persistent) launch of `fn`: every one must be
 // resident at once, since they meet at grid barriers.  The runtime's occupancy

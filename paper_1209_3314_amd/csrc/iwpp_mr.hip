@@ -1376,10 +1376,6 @@ int mr_launch(const MrArgs& a, int conn, int persistent_blocks, hipStream_t stre
       return -1;
     }
   }
-  if (zero_words(a.flags, 2ull * a.ntiles, stream) != 0) {
-    *err = "flag reset launch failed";
-    return -1;
-  }
   const int wpb = a.wg_waves == 8u ? 8 : 4;
   void* fn = wpb == 8 ? (conn == 8 ? reinterpret_cast<void*>(&k_propagate<8, 8>) : reinterpret_cast<void*>(&k_propagate<4, 8>))
                       : (conn == 8 ? reinterpret_cast<void*>(&k_propagate<8, 4>) : reinterpret_cast<void*>(&k_propagate<4, 4>));
