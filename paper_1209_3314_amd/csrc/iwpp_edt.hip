@@ -255,14 +255,27 @@ __device__ __forceinline__ void push(WgLds<WPB>& L, unsigned long long* now, uin
   unsigned long long* k = &L.key[at(row, col)];
   const uint32_t q = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u2, q0) + __builtin_bit_cast(u2, pack_yx(row, col)));
   const uint32_t b = Coord<kWide>::base(q, f);
+  // Four offers are on their way before the first answer is looked at; left to
+  // itself the compiler waits four times for eight (7001 x 5003 with
+  // 4-connectivity 2936 us, 2870; eight at once cost as many registers as they
+  // save waits).
   uint32_t took[3] = {0u, 0u, 0u};  // by row: bit 0 left, 1 same column, 2 right
 #pragma unroll
-  for (int n = 0; n < NC; ++n) {
-    const uint32_t step = ((uint32_t)kDy[n] << 16) | ((uint32_t)kDx[n] & 0xffffu);
-    const unsigned long long key = (unsigned long long)Coord<kWide>::d2_at(b, f, step) << 32 | f;
-    const unsigned long long old =
-        __hip_atomic_fetch_min(&k[kDy[n] * P + kDx[n]], key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    took[kDy[n] + 1] |= (old > key ? 1u : 0u) << (kDx[n] + 1);
+  for (int g = 0; g < NC; g += 4) {
+    unsigned long long old[4];
+    uint32_t d2[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int n = g + m;
+      const uint32_t step = ((uint32_t)kDy[n] << 16) | ((uint32_t)kDx[n] & 0xffffu);
+      d2[m] = Coord<kWide>::d2_at(b, f, step);
+      old[m] = __hip_atomic_fetch_min(&k[kDy[n] * P + kDx[n]], (unsigned long long)d2[m] << 32 | f, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      took[kDy[g + m] + 1] |= (old[m] > ((unsigned long long)d2[m] << 32 | f) ? 1u : 0u) << (kDx[g + m] + 1);
   }
 #pragma unroll
   for (int d = 0; d < 3; ++d)
@@ -305,7 +318,8 @@ __device__ __forceinline__ void relax_steps(WgLds<WPB>& L, const TileRef& tr, ui
     if (threadIdx.x == 0) L.any[(i + 1) & 1] = 0u;  // last read in round i-1, next set in round i+1
     uint32_t a = incl - c, b = a + (uint32_t)__popc(lo);
     const uint32_t r = (uint32_t)row << 6;
-    uint32_t ent[kParts * kPer], f[kParts * kPer];
+    uint32_t ent[kParts * kPer / 2], f[kParts * kPer];
+    static_assert(kPer % 2 == 0, "two entries a register");  // (4096^2: one spills 7 more, 1085 us against 1061)
 #pragma unroll
     for (int p = 0; p < kParts; ++p) {
       if (p > 0 && __builtin_expect(n <= (uint32_t)(p * kPart), 1)) break;  // wave-uniform
@@ -328,19 +342,20 @@ __device__ __forceinline__ void relax_steps(WgLds<WPB>& L, const TileRef& tr, ui
         if (q > 0 && n <= (uint32_t)(p * kPart + q * kWave)) break;
         const uint32_t idx = (uint32_t)(q * kWave + l);
         const uint32_t e = (uint32_t)(p * kPart) + idx < n ? (uint32_t)list[idx] : 0u;
-        ent[p * kPer + q] = e;
+        ent[(p * kPer + q) / 2] = q & 1 ? ent[(p * kPer + q) / 2] | e << 16 : e;
         f[p * kPer + q] = (uint32_t)L.key[at((int)(e >> 6), (int)(e & 63u))];
       }
       wave_sync();
     }
     __syncthreads();  // every source is read, the round's masks are clear
-    if (L.any[i & 1] == 0u) break;
+    const uint32_t any = L.any[i & 1];
 #pragma unroll
     for (int q = 0; q < kParts * kPer; ++q) {
       if (n <= (uint32_t)(q * kWave)) break;
-      if ((uint32_t)(q * kWave + l) < n) push<CONN, kWide, WPB>(L, now, ent[q], f[q], q0);
+      if ((uint32_t)(q * kWave + l) < n) push<CONN, kWide, WPB>(L, now, ent[q / 2] >> (16 * (q & 1)) & 0xffffu, f[q], q0);
     }
     __syncthreads();
+    if (any == 0u) break;  // (asked for here, the answer is not waited for)
   }
   const uint32_t c = (uint32_t)__popcll(L.chg[K & 1][row] & mine & own);
   changed += c;
