@@ -77,9 +77,11 @@ typedef struct {
    * paper varies the number of initial scans in Table 1; 0 = 1 with
    * 8-connectivity, 2 with 4-connectivity). */
   int32_t mr_seed_sweeps;
-  /* Waves per workgroup of the persistent kernels, 4 or 8 (0 = 4): the
-   * workgroup size (the paper's threads per block; a reconstruction tile is
-   * one wave's, a distance transform tile one workgroup's). */
+  /* Waves per workgroup of the persistent kernels, 4 or 8 (0 = automatic: 8
+   * for reconstructions and for distance transforms of at most 512 tiles of
+   * 48 x 48 in a launch, else 4): the workgroup size (the paper's threads per
+   * block; a reconstruction tile is one wave's, a distance transform tile one
+   * workgroup's). */
   int32_t wg_waves;
   /* Work-list items a wave stages in LDS before one global atomic appends
    * them (the depth of the paper's per-block queue): 1 .. 64 (0 = 64). */
