@@ -372,10 +372,10 @@ __device__ __forceinline__ WgShare wg_share(uint32_t n, uint32_t* next) {
 // A round's work list of tiles is split into kShards sub-lists, one per group of
 // workgroups (blockIdx & 7, i.e. one per XCD).  A wave stages its appends in LDS
 // and flushes them into its group's sub-list with one atomic on that sub-list's
-// counter, so each counter sees an eighth of the flushes.  Consumers read the
-// kShards counters and split the concatenation evenly over all waves, so a
-// round's work is balanced whatever the tiles' positions.  A per-tile flag word
-// (set with atomic_or) keeps a tile on a round's list at most once.
+// counter, so each counter sees an eighth of the flushes.  In the next round a
+// group consumes its own sub-list, whose tiles are neighbours of those it visited
+// last.  A per-tile flag word (set with atomic_or) keeps a tile on a round's list
+// at most once.
 constexpr int kShards = 8;
 
 // Counter of (round slot, shard): 256 bytes apart.

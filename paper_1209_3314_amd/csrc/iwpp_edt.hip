@@ -41,12 +41,12 @@
 //
 // Bound: 9 bytes a pixel have to move (30 us for 4096^2 at the copy rate); the
 // time goes to a visit's serial chain -- in cycles 5 k to load, per round 1.4 k
-// to list the sources and 0.9 k to push them, 5 k to store and list tiles --
+// to list the sources and 0.8 k to push them, 5 k to store and list tiles --
 // which four workgroups per CU (40 KB of keys each) hide in part, and to the
-// slowest visit of each step.  Measured (30% features, rounds kernel): 4096^2
-// 1050 us, 389 x 517 300 us.  Before, a pull over the neighbourhood of every
+// slowest visit of each step.  Measured (30% features, whole call): 4096^2 1060
+// us, 389 x 517 247 us.  Before, a pull over the neighbourhood of every
 // change (26 x 26 tiles, four rounds a visit, one wave each; eleven
-// evaluations of nine candidates per changed pixel): 1312 and 505 us.
+// evaluations of nine candidates per changed pixel): 1430 and 530 us.
 //
 // The tiles of a step are a work list split into eight sub-lists, one per
 // group of workgroups (one per XCD), appended to with one atomic per flush; a
@@ -629,8 +629,8 @@ __device__ __forceinline__ uint32_t steal(const uint32_t* lists, uint32_t stride
   }
 }
 
-// A workgroup of WPB waves per tile visit; four workgroups of four waves (or
-// three of eight) fit a CU's LDS.
+// A workgroup of WPB waves per tile visit; four workgroups of four waves fit a
+// CU's LDS, two of eight its registers.
 template <int CONN, bool kWide, int WPB>
 __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
   __shared__ WgLds<WPB> L;

@@ -84,7 +84,7 @@ struct EdtArgs {
   uint32_t* lists;            // [2][8 shards][ntiles] tile lists per round parity
   uint32_t* stamps;           // [2][ntiles] step of the tile's last visit, per step parity (0 = none)
   unsigned long long* marks;  // [2][ntiles][kEdtMarkWords] that visit's last-round change mask
-  uint32_t* counts;           // [3 round slots][8 shards][64] list fill levels (256 B apart)
+  uint32_t* counts;           // [3 round slots][8 shards][64] list fill levels (256 B apart; word 32: items taken)
   uint32_t* ovf;              // never set: a list holds each tile once
   uint32_t stage_depth;       // work-list items staged per wave before a flush (0 = the LDS maximum)
   uint32_t wg_waves;          // waves per workgroup of the rounds kernel: 4 or 8

@@ -11,9 +11,10 @@
 //   round 0  -- the seed pass: every tile is loaded from the marker (clamped
 //               to the mask) and swept with Algorithm 5's raster and
 //               anti-raster scans, split into row-wise and column-wise
-//               sweeps, until it is locally stable (lane = row or column);
+//               sweeps (lane = row or column), until it is locally stable
+//               or a cap of sweep iterations is reached;
 //   round r  -- each tile flagged in round r-1 is loaded from the current
-//               image, swept to local stability and written back.
+//               image, swept the same way and written back.
 // After a visit the wave flags each neighbouring tile that a border change
 // can still raise (Algorithm 5's propagation condition, J(q) < J(p) and
 // J(q) < I(q), tested against the halo as loaded), and the tile itself if the
@@ -25,9 +26,9 @@
 // The tile frontier of a round is a work list split into eight sub-lists, one
 // per group of workgroups (one per XCD): a wave stages its appends in LDS and
 // flushes them with one atomic on its group's counter, a per-tile flag keeps a
-// tile on a round's list once, and the next round splits the concatenated
-// sub-lists evenly over all waves, so a round's visits are balanced.  With a
-// capacity (the paper's fixed-size global queue, Sec. 3.2) the list is one
+// tile on a round's list once, and in the next round an XCD visits its own
+// sub-list, cut into one share per workgroup whose waves take tiles as they get
+// to them.  With a capacity (the paper's fixed-size global queue, Sec. 3.2) the list is one
 // sub-list of that size: an append past it is dropped and flagged, and the
 // next round becomes a full round that visits every tile holding a raisable
 // pixel of the current image, which is a valid restart point because every
@@ -39,6 +40,14 @@
 // atomics touch pixels.  Halo reads may see a neighbour mid-update; any value
 // they see is a valid lower bound, and a border change always re-lists the
 // neighbour for the next round, which then reads it after a grid barrier.
+//
+// Bound: three bytes a pixel have to move (158 us for 16384^2 at the copy rate);
+// the time goes to the scans' dependence chains, which four waves per SIMD (9
+// KiB of LDS and 128 registers each) do not hide -- VALU issue is a little over
+// half -- and, with few tiles, to one visit and one barrier a round.  Measured
+// (16384^2 with 8- and 4-connectivity, 4096^2 and 512^2): 1370, 1350, 258, 114
+// us; before scans ran in pairs on lines in registers, with a barrier of seven
+// round trips and seed strips only: 1510, 1720, 345, 141.
 #include "iwpp_device.hpp"
 #include "iwpp_internal.hpp"
 
@@ -1211,8 +1220,8 @@ __device__ __forceinline__ uint32_t auto_strip(const MrArgs& a, int conn, uint32
 // Round 0 is the seed pass over every tile; round r >= 1 visits the tiles
 // listed in round r-1 and lists the tiles of round r+1 (parity (r+1)&1,
 // count slot (r+1)%3).  The list is split over kShards sub-lists, one per
-// group of workgroups; a round's items (the concatenated sub-lists) are cut
-// into one share per workgroup (WgShare).  Bounded mode (a capacity below
+// group of workgroups; a group's sub-list is cut into one share per
+// workgroup (WgShare).  Bounded mode (a capacity below
 // the tile count) uses one sub-list of that capacity; a round whose list
 // lost tiles is replaced by a full round that visits every tile holding a
 // raisable pixel (all flags cleared first), restarting from the current
