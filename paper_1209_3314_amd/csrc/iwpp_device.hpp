@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "iwpp_barrier.hpp"
+
 namespace iwpp {
 
 constexpr int kWave = 64;
@@ -152,34 +154,25 @@ __device__ __forceinline__ void stat_add(unsigned long long* stats, int field, u
 }
 
 // ---- grid barrier ---------------------------------------------------------------
-// Counting barrier for a co-resident (cooperative) grid: a workgroup counts
-// itself in one of 8 group counters (blockIdx & 7, 256 bytes apart so they do
-// not share a cache line), the last of a group writes the group's generation,
-// and everyone polls the eight generations -- one cache line -- with the abort
-// word in the same load.  Every wait is bounded: on timeout (or when another
-// workgroup raised `abort`) the barrier returns false and the caller must leave
-// the kernel.
+// Counting barrier for a co-resident (cooperative) grid (state and protocol:
+// iwpp_barrier.hpp).  A workgroup counts itself in one of 8 group counters
+// (blockIdx & 7), the last of a group writes the group's word of this generation,
+// and everyone polls the eight words -- half a cache line -- with the abort word in
+// the same load.  Every wait is bounded: on timeout (or when another workgroup
+// raised `abort`) the barrier returns false and the caller must leave the kernel.
 //
 // A round with few tiles is mostly latencies, so the barrier has two memory
-// round trips on its path.  Counters only grow (arrival (gen + 1) * size is a
-// generation's last): nothing is reset, and nothing has to be written before the
-// generation.  Before, with a counter over the groups, resets, and generation,
-// abort word and result read one after the other, a 389 x 517 transform (12
-// steps) took 325 us, now 309; a 4096^2 reconstruction 340 and 331, 32 small
-// images 1195 and 1164.
+// round trips on its path.  Counters only grow: nothing is reset, and nothing has
+// to be written before the generation.  Before, with a counter over the groups,
+// resets, and generation, abort word and result read one after the other, a
+// 389 x 517 transform (12 steps) took 325 us, now 309; a 4096^2 reconstruction 340
+// and 331, 32 small images 1195 and 1164.
 //
-// The high half of a group's counter and word is the number of list items its
-// workgroups have appended, carried along with the arrivals, so that a round
-// begins with its lists' lengths known and no more loads.  With it, and with
-// shares cut without 64-bit divisions and items read from the group's own
-// sub-list without a search, a reconstruction of 512 x 512 went from 143 to 120
-// us, 1500 x 1301 187 to 165, 4096^2 307 to 282, 65536 x 65600 15990 to 14730.
-struct GridBarrier {
-  unsigned long long group[8][32];
-  unsigned long long word[32];  // [x]: group x's items << 32 | generation
-  uint32_t abort[64];
-};
-
+// The items appended travel with the arrivals, so that a round begins with its
+// lists' lengths known and no more loads.  With it, and with shares cut without
+// 64-bit divisions and items read from the group's own sub-list without a search,
+// a reconstruction of 512 x 512 went from 143 to 120 us, 1500 x 1301 187 to 165,
+// 4096^2 307 to 282, 65536 x 65600 15990 to 14730.
 constexpr uint32_t kSpinLimit = 1u << 24;  // ~ seconds of polling, far beyond any real wait
 
 // What the kernel's workgroup has appended since the last barrier (LDS), and
@@ -201,10 +194,11 @@ __device__ __forceinline__ bool grid_barrier(GridBarrier* b, uint32_t& gen, unsi
   if (threadIdx.x < (unsigned)kWave) {  // wave 0
     const uint32_t nwg = gridDim.x, g = blockIdx.x & 7u, in_group = (nwg - g + 7u) >> 3, groups = nwg < 8u ? nwg : 8u;
     const uint32_t l = (uint32_t)local_copy((int)threadIdx.x);
+    unsigned long long* words = b->word[barrier::slot(gen)];
     if (l == 0u) {
-      const unsigned long long one = (app ? (unsigned long long)*app->here << 32 : 0ull) | 1ull;
+      const unsigned long long one = barrier::arrival(app ? *app->here : 0u);
       const unsigned long long total = atomic_add(&b->group[g][0], one) + one;
-      if ((uint32_t)total == (gen + 1u) * in_group) cstore(&b->word[g], (total & ~0xFFFFFFFFull) | (gen + 1u));
+      if (barrier::last(total, gen, in_group)) cstore(&words[g], barrier::word(total, gen));
       if (app) {
         *app->here = 0u;
         if (app->zero) *app->zero = 0u;
@@ -214,13 +208,13 @@ __device__ __forceinline__ bool grid_barrier(GridBarrier* b, uint32_t& gen, unsi
     uint32_t res = 1;
     for (uint32_t spins = 0;;) {
       uint32_t stop = 0u;
-      if (l < groups) v = cload(&b->word[l]);
+      if (l < groups) v = cload(&words[l]);
       if (l == groups) stop = cload(&b->abort[0]);
       if (ballot(stop != 0u) != 0ull) {
         res = 0;
         break;
       }
-      if (ballot(l < groups && (uint32_t)v == gen) == 0ull) break;
+      if (ballot(l < groups && !barrier::arrived(v, gen)) == 0ull) break;
       __builtin_amdgcn_s_sleep(2);
       if (++spins > kSpinLimit) {
         if (l == 0u) {
@@ -232,7 +226,7 @@ __device__ __forceinline__ bool grid_barrier(GridBarrier* b, uint32_t& gen, unsi
       }
     }
     if (app && l < 8u) {
-      const uint32_t items = (uint32_t)(v >> 32);
+      const uint32_t items = barrier::items(v);
       app->cnt[l] = items - app->seen;
       app->seen = items;
     }
