@@ -110,9 +110,10 @@ size_t job_scratch_bytes(int op, int32_t h, int32_t w) {
   const uint64_t t = (uint64_t)((h + ts - 1) / ts) * (uint64_t)((w + ts - 1) / ts);
   const uint64_t np = (uint64_t)h * (uint64_t)w;
   // 20 tile words, and per tile 256 bytes of recon border columns or the
-  // EDT's two visit stamps and change records (+ alignment slack of the per-group
-  // arrays is added by the caller)
-  return (size_t)(80 * t + 20 * 256 + (op == IWPP_OP_EDT ? 8 * np + 2 * iwpp::kEdtStatePad + (8 + 16 * iwpp::kEdtMarkWords) * t : 256 * t) +
+  // EDT's two visit stamps, and its change records (+ alignment slack of the
+  // per-group arrays is added by the caller)
+  return (size_t)(80 * t + 20 * 256 +
+                  (op == IWPP_OP_EDT ? 8 * np + 2 * iwpp::kEdtStatePad + 8 * t + 16 * iwpp::edt_mark_words(h, w) : 256 * t) +
                   (op == IWPP_OP_RECON ? sizeof(iwpp::MrJob) : sizeof(iwpp::EdtJob)));
 }
 
@@ -136,13 +137,15 @@ void mr_place(iwpp::MrJob& m, uint64_t& tiles) {
   tiles += (uint64_t)m.tiles_y * (uint64_t)m.tiles_x;
 }
 
-void edt_place(iwpp::EdtJob& e, uint64_t& pix, uint64_t& tiles) {
+void edt_place(iwpp::EdtJob& e, uint64_t& pix, uint64_t& tiles, uint64_t& marks) {
   e.tiles_y = (e.h + iwpp::kEdtTile - 1) / iwpp::kEdtTile;
   e.tiles_x = (e.w + iwpp::kEdtTile - 1) / iwpp::kEdtTile;
   e.tile_base = (uint32_t)tiles;
   e.pix_base = pix;
+  e.mark_base = (uint32_t)marks;  // 2^32 words are 32 GB of records, for more pixels than the memory holds
   tiles += (uint64_t)e.tiles_y * (uint64_t)e.tiles_x;
   pix += (uint64_t)e.h * (uint64_t)e.w;
+  marks += iwpp::edt_mark_words(e.h, e.w);
 }
 
 // Validate the jobs and group them by (op, conn).  `who` prefixes messages.
@@ -222,7 +225,7 @@ int32_t build_plan(iwpp_ctx* ctx, const iwpp_job* jobs, int32_t n, const char* w
           e.nearest = static_cast<int32_t*>(j.out1);
           e.h = j.height;
           e.w = j.width;
-          edt_place(e, g.npix, g.ntiles);
+          edt_place(e, g.npix, g.ntiles, g.mark_words);
           g.edt.push_back(e);
         }
       }
@@ -322,6 +325,7 @@ int32_t launch_group(iwpp_ctx* ctx, const Group& g, uint8_t* scratch, uint8_t* f
     a.job0 = g.edt[0];
     a.njobs = nj;
     a.npix = g.npix;
+    a.mark_words = (uint32_t)g.mark_stride();
     a.wide = 0;
     for (const iwpp::EdtJob& e : g.edt)
       if (e.h > 32767 || e.w > 32767) a.wide = 1;

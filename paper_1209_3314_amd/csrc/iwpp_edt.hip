@@ -76,7 +76,8 @@ constexpr uint32_t kMaxSteps = (1u << 20) / K;
 static_assert(R == 64, "one mask bit per region column, one lane per region row");
 static_assert(K % 4 == 0 && TE % 4 == 0, "16-byte chunks must not straddle the image's left edge or a tile's");
 static_assert(K <= TE, "a change must reach no farther than the neighbouring tiles");
-static_assert(TE == kEdtTile && TE <= 64, "change records are one 64-bit word per tile row");
+static_assert(K <= 8, "a change record's shortest word holds the columns a neighbour looks at");
+static_assert(TE == kEdtTile && TE <= 64, "change records are one word of at most 64 bits per tile row");
 
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -369,6 +370,35 @@ __device__ __forceinline__ void relax_steps(WgLds<WPB>& L, const TileRef& tr, ui
 // stamp differs did not change.  One wave, lane = region row: the stamps and
 // row words of three tiles (left neighbour, own column, right neighbour).
 // Split in two so that the loads are in flight with the region's.
+//
+// Row y's word of a tile column is word y of the column's run (`edt_mark_words`).
+// Words of every width are read alike, as the 8 bytes that begin there, and cut to
+// the column's bits, with no branch on the width or on the image's edges (7001 x
+// 5003 with 4-connectivity 2750 us; loads of each width behind branches 2912; 48
+// words of 8 bytes a tile, whatever its size, 2723; 4096^2 1119, 1118 and 1125).
+__device__ __forceinline__ int mark_cols(const EdtJob& j, int tx) { return tx + 1 < j.tiles_x ? TE : j.w - tx * TE; }
+__device__ __forceinline__ uint32_t mark_offset(const EdtJob& j, int tx, int y) {
+  return (uint32_t)tx * (uint32_t)j.h * 8u + ((uint32_t)y << edt_mark_shift(mark_cols(j, tx)));
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t marks_rsrc(const EdtArgs& a, const EdtJob& j, uint32_t par) {
+  // No image has more than tiles_x full columns' runs; 8 bytes are read at the last word.
+  return make_rsrc(a.marks + (size_t)par * a.mark_words + j.mark_base, (uint32_t)j.tiles_x * (uint32_t)j.h * 8u + 8u);
+}
+
+// Every lane with `ok`: m as row y's word, by the one of four stores of its width;
+// the others go outside the buffer.
+__device__ __forceinline__ void store_mark(const EdtArgs& a, const TileRef& tr, uint32_t par, bool ok, int y,
+                                           unsigned long long m) {
+  const __amdgpu_buffer_rsrc_t rm = marks_rsrc(a, tr.j, par);
+  const int sh = edt_mark_shift(mark_cols(tr.j, tr.tx));
+  const uint32_t off = ok ? mark_offset(tr.j, tr.tx, y) : kOutside;
+  typedef unsigned v2u __attribute__((ext_vector_type(2)));
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, m), rm, sh == 3 ? off : kOutside, 0, kSc1);
+  __builtin_amdgcn_raw_buffer_store_b32((uint32_t)m, rm, sh == 2 ? off : kOutside, 0, kSc1);
+  __builtin_amdgcn_raw_buffer_store_b16((uint16_t)m, rm, sh == 1 ? off : kOutside, 0, kSc1);
+  __builtin_amdgcn_raw_buffer_store_b8((uint8_t)m, rm, sh == 0 ? off : kOutside, 0, kSc1);
+}
+
 struct PrevChanges {
   uint32_t stamp[3];
   unsigned long long word[3];
@@ -379,26 +409,28 @@ __device__ __forceinline__ void prev_step_issue(const EdtArgs& a, const TileRef&
   const uint32_t par = (m - 1u) & 1u;
   const int y = tr.ty * TE - K + lane();
   const bool row_ok = y >= 0 && y < j.h;
-  const int ty = row_ok ? y / TE : 0, ly = row_ok ? y - ty * TE : 0;
+  const int ty = row_ok ? y / TE : 0;
+  const __amdgpu_buffer_rsrc_t rm = marks_rsrc(a, j, par);
+  const __amdgpu_buffer_rsrc_t rt =
+      make_rsrc(a.stamps + (size_t)par * a.ntiles + j.tile_base, (uint32_t)j.tiles_y * (uint32_t)j.tiles_x * 4u);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const int tx = tr.tx + d - 1;
-    pc.stamp[d] = 0u;
-    pc.word[d] = 0ull;
-    if (row_ok && tx >= 0 && tx < j.tiles_x) {
-      const uint32_t u = j.tile_base + (uint32_t)(ty * j.tiles_x + tx);
-      pc.stamp[d] = cload(a.stamps + (size_t)par * a.ntiles + u);
-      pc.word[d] = cload(a.marks + ((size_t)par * a.ntiles + u) * kEdtMarkWords + (uint32_t)ly);
-    }
+    const bool ok = row_ok && tx >= 0 && tx < j.tiles_x;
+    const uint32_t so = ok ? (uint32_t)(ty * j.tiles_x + tx) * 4u : kOutside, off = ok ? mark_offset(j, tx, y) : kOutside;
+    pc.stamp[d] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rt, so, 0, kSc1);
+    pc.word[d] = __builtin_bit_cast(unsigned long long, __builtin_amdgcn_raw_buffer_load_b64(rm, off, 0, kSc1));
   }
 }
 
-__device__ __forceinline__ void prev_step_finish(uint32_t m, const PrevChanges& pc, unsigned long long* M) {
+__device__ __forceinline__ void prev_step_finish(const TileRef& tr, uint32_t m, const PrevChanges& pc,
+                                                 unsigned long long* M) {
   unsigned long long v = 0;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     if (pc.stamp[d] != m - 1u) continue;
-    const unsigned long long w = pc.word[d];
+    // (the left column is a full one, and of the right one K columns are wanted, no more than its shortest word has)
+    const unsigned long long w = d == 1 ? pc.word[d] & ((1ull << mark_cols(tr.j, tr.tx)) - 1ull) : pc.word[d];
     // region column rx <-> tile column rx - K - (d - 1) * TE
     v |= d == 0 ? (w >> (TE - K)) : (d == 1 ? (w << K) : ((w & ((1ull << K) - 1ull)) << (K + TE)));
   }
@@ -408,11 +440,11 @@ __device__ __forceinline__ void prev_step_finish(uint32_t m, const PrevChanges& 
 // Record this visit's last-round changes of the tile (rows and columns
 // [K, K + TE) of the round-K mask word `m` of region row lane()) and stamp
 // them with step `step`.
-__device__ __forceinline__ void record_changes(const EdtArgs& a, uint32_t t, uint32_t step, unsigned long long m) {
-  const int l = lane();
+__device__ __forceinline__ void record_changes(const EdtArgs& a, const TileRef& tr, uint32_t t, uint32_t step,
+                                               unsigned long long m) {
+  const int l = lane(), y = tr.ty * TE + l - K;
   const uint32_t par = step & 1u;
-  if (l >= K && l < K + TE)
-    cstore(a.marks + ((size_t)par * a.ntiles + t) * kEdtMarkWords + (uint32_t)(l - K), (m & kTileCols) >> K);
+  store_mark(a, tr, par, l >= K && l < K + TE && y < tr.j.h, y, (m & kTileCols) >> K);
   if (l == 0) cstore(a.stamps + (size_t)par * a.ntiles + t, step);
 }
 
@@ -559,7 +591,7 @@ __global__ __launch_bounds__(256) void k_init(EdtArgs a) {
     }
   }
   if (w == 0) {
-    if (mine) cstore(a.marks + (size_t)t * kEdtMarkWords + (uint32_t)(l - 1), ct >> 1);
+    store_mark(a, tr, 0u, mine && y0 + l < j.h, y0 + l, ct >> 1);
     const uint32_t contour = wave_incl_sum((uint32_t)__popcll(ct));
     if (l == kWave - 1 && contour) {
       stat_add(a.stats, kStatSeeds, contour);
@@ -706,7 +738,7 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
         prev_step_issue(a, tr, m, pc);
       }
       load_region<kWide, WPB>(rd, tr, L);
-      if (w == 0) prev_step_finish(m, pc, L.chg[0]);
+      if (w == 0) prev_step_finish(tr, m, pc, L.chg[0]);
       uint32_t t_next = kNoTile;
       if (threadIdx.x == 0 && i < cnt[grp]) t_next = cload(lists + (size_t)grp * a.ntiles + i);
       __syncthreads();
@@ -724,7 +756,7 @@ __global__ __launch_bounds__(64 * WPB, 4) void k_rounds(EdtArgs a) {
       if (w == 0) {
         visits++;
         const unsigned long long mk = L.chg[K & 1][lane()];
-        record_changes(a, t, m, mk);
+        record_changes(a, tr, t, m, mk);
         const uint32_t lw = readlane(last_sh, 0);
         wave_sync();
         if (lane() == 0) last_sh = 0u;

@@ -12,7 +12,16 @@ struct GridBarrier;
 constexpr int kMrTile = 64;   // reconstruction tiles: 64 x 64 pixels
 constexpr int kEdtHalo = 8;   // EDT rounds per tile visit (= halo width)
 constexpr int kEdtTile = 48;  // EDT tiles: 48 x 48 pixels (a 64 x 64 region with the halo)
-constexpr int kEdtMarkWords = kEdtTile;  // 64-bit words of a tile's change record, one per row
+// EDT change records: for every column of tiles one run of row words, a bit per
+// pixel of the row in that column; a narrow last column takes shorter words, and
+// there are no more rows than the image has.  (48 words of 8 bytes a tile whatever
+// its size would be 16 bytes a row of an image one pixel wide, where this is 2.)
+constexpr int edt_mark_shift(int cols) { return cols > 32 ? 3 : (cols > 16 ? 2 : (cols > 8 ? 1 : 0)); }
+// 8-byte words of an image's records, with one more: words are read as 8 bytes each.
+constexpr uint64_t edt_mark_words(int32_t h, int32_t w) {
+  const int32_t full = (w - 1) / kEdtTile;  // tile columns before the last
+  return (uint64_t)full * (uint64_t)h + (((uint64_t)h << edt_mark_shift(w - full * kEdtTile)) + 7) / 8 + 1;
+}
 constexpr size_t kEdtStatePad = 256;  // bytes after each EDT state buffer (16-byte loads may cross the end)
 
 // One reconstruction image of a launch.
@@ -63,7 +72,7 @@ struct EdtJob {
   int32_t h, w;
   int32_t tiles_y, tiles_x;  // kEdtTile x kEdtTile tiles
   uint32_t tile_base;        // first global tile id of this image
-  uint32_t pad;
+  uint32_t mark_base;        // first word of this image's change records
   unsigned long long pix_base;  // first global pixel id of this image
 };
 
@@ -76,14 +85,14 @@ struct EdtArgs {
   uint32_t njobs;
   uint32_t ntiles;
   uint32_t wide;              // nonzero: wide coordinate fields (an image side above 32767)
-  uint32_t pad0;
+  uint32_t mark_words;        // 8-byte words of change records of all images (one step parity)
   unsigned long long npix;    // total pixels over all images
   uint32_t* feat0;            // [npix] nearest feature (y << 16 | x), ~0 = none; round parity 0
   uint32_t* feat1;            // [npix] round parity 1
   uint32_t* flags;            // [2][ntiles] tile on the round's list, per round parity
   uint32_t* lists;            // [2][8 shards][ntiles] tile lists per round parity
   uint32_t* stamps;           // [2][ntiles] step of the tile's last visit, per step parity (0 = none)
-  unsigned long long* marks;  // [2][ntiles][kEdtMarkWords] that visit's last-round change mask
+  unsigned long long* marks;  // [2][mark_words] that visit's last-round changes (see edt_mark_words)
   uint32_t* counts;           // [3 round slots][8 shards][64] list fill levels (256 B apart; word 32: items taken)
   uint32_t* ovf;              // never set: a list holds each tile once
   uint32_t stage_depth;       // work-list items staged per wave before a flush (0 = the LDS maximum)

@@ -32,6 +32,7 @@ struct Group {
   std::vector<iwpp::EdtJob> edt;
   uint64_t ntiles = 0;
   uint64_t npix = 0;
+  uint64_t mark_words = 0;  // EDT change records
   size_t table_off = 0;  // offset of this group's job table in the table area
 
   uint32_t njobs() const { return (uint32_t)(op == IWPP_OP_RECON ? mr.size() : edt.size()); }
@@ -39,12 +40,14 @@ struct Group {
     return njobs() > 1 ? align256(op == IWPP_OP_RECON ? mr.size() * sizeof(iwpp::MrJob) : edt.size() * sizeof(iwpp::EdtJob))
                        : 0;
   }
+  // Words of one step parity's change records: whole cache lines.
+  uint64_t mark_stride() const { return (mark_words + 15) & ~uint64_t(15); }
   // Scratch layout (T = tiles, arrays of u32, each 256-byte aligned).
   // Recon: flags[2][T] | lists[2][8][T] | unsettled[T] | tile_job[T] | cols[T][256 B].
-  // EDT: feat0 | feat1 | flags[2][T] | lists[2][8][T] | tile_job[T] | stamps[2][T] | marks[2][T][8 kEdtMarkWords B].
+  // EDT: feat0 | feat1 | flags[2][T] | lists[2][8][T] | tile_job[T] | stamps[2][T] | marks[2][mark_stride()][8 B].
   size_t scratch_bytes() const {
     const size_t tb = align256(ntiles * 4);
-    return op == IWPP_OP_EDT ? 2 * (align256(npix * 4) + iwpp::kEdtStatePad) + 21 * tb + ntiles * 16 * iwpp::kEdtMarkWords
+    return op == IWPP_OP_EDT ? 2 * (align256(npix * 4) + iwpp::kEdtStatePad) + 21 * tb + 16 * mark_stride()
                              : 20 * tb + ntiles * 256;
   }
 };
