@@ -66,7 +66,8 @@ typedef struct {
   /* Cap on sweep iterations per tile visit before the tile is re-queued
    * (0 = 4). */
   int32_t mr_max_sweeps;
-  /* Workgroups of the persistent kernels (0 = fill the device). */
+  /* Workgroups of the persistent kernels, at most (0 = fill the device).  With a
+   * cap and wg_waves 0 a workgroup has four waves. */
   int32_t persistent_blocks;
   /* Nonzero: record a HIP event pair around every kernel launch so that
    * iwpp_profile_read can report per-kernel device times.  Costs two event
@@ -79,7 +80,7 @@ typedef struct {
   int32_t mr_seed_sweeps;
   /* Waves per workgroup of the persistent kernels, 4 or 8 (0 = automatic: 8
    * for reconstructions and for distance transforms of at most 512 tiles of
-   * 48 x 48 in a launch, else 4): the workgroup size (the paper's threads per
+   * 48 x 48 in a launch, else 4; with persistent_blocks set, 4): the workgroup size (the paper's threads per
    * block; a reconstruction tile is one wave's, a distance transform tile one
    * workgroup's). */
   int32_t wg_waves;

@@ -302,11 +302,7 @@ int32_t launch_group(iwpp_ctx* ctx, const Group& g, uint8_t* scratch, uint8_t* f
     a.seed_only = seed_only ? 1u : 0u;
     a.seed_strip = (uint32_t)ctx->opt.mr_seed_strip;
     a.stage_depth = (uint32_t)ctx->opt.stage_depth;
-    // Eight waves: twice as many take tiles from one workgroup's share, and half
-    // as many workgroups meet at the barrier (us with 4, 8: 16384^2 1456, 1374
-    // and with 4-connectivity 1431, 1347; 4096^2 269, 258; 65536 x 65600 12880,
-    // 12200; 1500 x 1301 154, 149; 512^2 114, 114; 20000 x 17000 2276, 2299).
-    a.wg_waves = ctx->opt.wg_waves == 4 ? 4u : 8u;
+    a.wg_waves = iwpp::recon_waves(ctx->opt.wg_waves, ctx->opt.persistent_blocks);
     a.flags = reinterpret_cast<uint32_t*>(scratch);
     a.lists = reinterpret_cast<uint32_t*>(scratch + 2 * tb);
     a.unsettled = reinterpret_cast<uint32_t*>(scratch + 18 * tb);
@@ -341,12 +337,7 @@ int32_t launch_group(iwpp_ctx* ctx, const Group& g, uint8_t* scratch, uint8_t* f
     a.counts = reinterpret_cast<uint32_t*>(fixed + kOffCounts);
     a.ovf = reinterpret_cast<uint32_t*>(fixed + kOffOvf);
     a.stage_depth = (uint32_t)ctx->opt.stage_depth;
-    // A workgroup's waves share a tile.  Where every tile has a workgroup of
-    // eight waves (two fit a CU) a visit is shorter with eight (us with 4, 8: 99
-    // tiles 290, 247; 441 tiles 295, 281; 529 tiles 317, 292); with more tiles
-    // than that four workgroups of four hide more (625 tiles 380, 391; 4096^2
-    // 1064, 1391).
-    a.wg_waves = ctx->opt.wg_waves == 8 || (ctx->opt.wg_waves == 0 && g.ntiles <= 512) ? 8u : 4u;
+    a.wg_waves = iwpp::edt_waves(ctx->opt.wg_waves, ctx->opt.persistent_blocks, g.ntiles);
     a.bar = reinterpret_cast<iwpp::GridBarrier*>(fixed + kOffBarrier);
     a.stats = reinterpret_cast<unsigned long long*>(fixed + kOffStats);
     a.clock = reinterpret_cast<unsigned long long*>(fixed + kOffClock);

@@ -112,6 +112,27 @@ constexpr int kClockWords = 512;
 constexpr size_t kLostBytes = 2 * 64 * 4;
 constexpr size_t kStatsBytes = 8 * 16 * 8;
 
+// Waves per workgroup of the persistent kernels (iwpp_options.wg_waves, 0 =
+// automatic).  A caller that caps the workgroups (iwpp_options.persistent_blocks)
+// has sized its cap for four waves each, so the automatic choice is four then: with
+// eight, half the device would have become all of it.
+//
+// Reconstruction, eight waves: twice as many take tiles from one workgroup's
+// share, and half as many workgroups meet at the barrier (us with 4, 8: 16384^2
+// 1456, 1374 and with 4-connectivity 1431, 1347; 4096^2 269, 258; 65536 x 65600
+// 12880, 12200; 1500 x 1301 154, 149; 512^2 114, 114; 20000 x 17000 2276, 2299).
+constexpr uint32_t recon_waves(int32_t wg_waves, int32_t persistent_blocks) {
+  return wg_waves == 4 || (wg_waves == 0 && persistent_blocks > 0) ? 4u : 8u;
+}
+// Distance transform: a workgroup's waves share a tile.  Where every tile has a
+// workgroup of eight waves (two fit a CU) a visit is shorter with eight (us with
+// 4, 8: 99 tiles 290, 247; 441 tiles 295, 281; 529 tiles 317, 292); with more tiles
+// than that four workgroups of four hide more (625 tiles 380, 391; 4096^2 1064,
+// 1391).
+constexpr uint32_t edt_waves(int32_t wg_waves, int32_t persistent_blocks, uint64_t ntiles) {
+  return wg_waves == 8 || (wg_waves == 0 && persistent_blocks == 0 && ntiles <= 512) ? 8u : 4u;
+}
+
 // Optional per-launch event timing (iwpp_options.profile).  begin/end bracket
 // one kernel launch on `s`; both are no-ops when disabled or full.
 class Recorder {

@@ -33,15 +33,15 @@ DEFAULTS = {"persistent_blocks": 0, "mr_max_sweeps": 0, "mr_seed_sweeps": 0, "mr
             "stage_depth": 0, "mr_seed_strip": 0}
 
 # Candidate grids.  0 means the library default (device-filling grid, the
-# workgroup size by operation and size, the deepest LDS stage, automatic strips,
-# default sweep caps).
+# workgroup size by operation and size -- four waves under a cap on the
+# workgroups --, the deepest LDS stage, automatic strips, default sweep caps).
+_GRIDS = [(0, 0), (4, 0), (8, 0), (4, 512), (8, 512)]  # wg_waves, persistent_blocks
 GRID = {
     "recon": [{"wg_waves": wg, "stage_depth": sd, "mr_seed_strip": sp, "mr_max_sweeps": ms, "mr_seed_sweeps": ss}
               for wg in (0, 4) for sd in (0, 16) for sp in (0, 4, 16) for ms in (0, 1) for ss in (0, 2)],
-    "edt": [{"wg_waves": wg, "stage_depth": sd, "persistent_blocks": pb}
-            for wg in (0, 4, 8) for sd in (0, 16) for pb in (0, 512)],
+    "edt": [{"wg_waves": wg, "stage_depth": sd, "persistent_blocks": pb} for wg, pb in _GRIDS for sd in (0, 16)],
     "batch": [{"wg_waves": wg, "stage_depth": sd, "mr_max_sweeps": ms, "persistent_blocks": pb}
-              for wg in (0, 4, 8) for sd in (0, 16) for ms in (0, 1) for pb in (0, 512)],
+              for wg, pb in _GRIDS for sd in (0, 16) for ms in (0, 1)],
 }
 
 

@@ -1,0 +1,14 @@
+// Waves per workgroup for "wg_waves persistent_blocks tiles" triples given as
+// arguments: reconstruction, distance transform.  Host code only.
+#include <cstdio>
+#include <cstdlib>
+
+#include "iwpp_internal.hpp"
+
+int main(int argc, char** argv) {
+  for (int i = 1; i + 2 < argc; i += 3) {
+    const int waves = std::atoi(argv[i]), blocks = std::atoi(argv[i + 1]);
+    std::printf("%u %u\n", iwpp::recon_waves(waves, blocks), iwpp::edt_waves(waves, blocks, std::strtoull(argv[i + 2], nullptr, 10)));
+  }
+  return 0;
+}
