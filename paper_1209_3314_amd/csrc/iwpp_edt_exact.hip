@@ -45,6 +45,11 @@ constexpr int kSerial = 64;   // longest range one lane searches alone
 constexpr uint32_t kFar = 46341u;  // stands for "no feature in the column": its square is above every real one,
                                    // and stays below 2^32 with a column distance's square added
 
+// LDS of the row pass for rows w wide: 3 bytes a column.
+constexpr uint32_t row_lds(uint32_t w) { return 2u * (w + (w + 1u) / 2u); }
+constexpr uint32_t kMaxRowLds = row_lds(46340);  // the widest row accepted
+static_assert(kMaxRowLds <= 160u * 1024u, "a CU's LDS");
+
 struct XArgs {
   const uint8_t* bin;  // 0 = feature
   int32_t* sqdist;
@@ -316,10 +321,12 @@ extern "C" int32_t iwpp_edt_exact(iwpp_ctx* ctx, const uint8_t* binary, int32_t*
   // Rows wider than 8192 take 1024 threads: their 3 bytes of LDS a column leave
   // room for few workgroups per CU.  Rows up to 512 take one wave each.
   const int threads = width > 8192 ? 1024 : (width > 512 ? 256 : 64);
-  const uint32_t lds = 2u * ((uint32_t)width + ((uint32_t)width + 1u) / 2u);
+  const uint32_t lds = xedt::row_lds((uint32_t)width);
   void (*row)(xedt::XArgs) = threads == 1024 ? &xedt::k_row<1024> : (threads == 256 ? &xedt::k_row<256> : &xedt::k_row<64>);
+  // The kernel's limit belongs to the process: always the same value, so that a call
+  // of another thread with narrower rows cannot lower it between here and the launch.
   if (lds > 64u * 1024u && hipFuncSetAttribute(reinterpret_cast<const void*>(row), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)lds) != hipSuccess) {
+                                               (int)xedt::kMaxRowLds) != hipSuccess) {
     (void)hipGetLastError();
     return fail(ctx, IWPP_EDEVICE, "edt_exact: the row pass's LDS is not available");
   }
