@@ -48,10 +48,6 @@ __device__ __forceinline__ T atomic_or(T* p, T v) {
   return __hip_atomic_fetch_or(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <typename T>
-__device__ __forceinline__ T atomic_min(T* p, T v) {
-  return __hip_atomic_fetch_min(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
 __device__ __forceinline__ T atomic_max(T* p, T v) {
   return __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -95,14 +91,6 @@ __device__ __forceinline__ uint32_t from_left(uint32_t v, uint32_t fill) {
 // lane i receives v from lane i+1; lane 63 receives `fill`.
 __device__ __forceinline__ uint32_t from_right(uint32_t v, uint32_t fill) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)fill, (int)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, false);
-}
-// lane i receives v from lane i-1 (i+1); lane 0 (63) receives 0, the identity
-// of an unsigned max, so a max of the result folds into one DPP instruction.
-__device__ __forceinline__ uint32_t from_left0(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x138 /* wave_shr:1 */, 0xf, 0xf, true);
-}
-__device__ __forceinline__ uint32_t from_right0(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x130 /* wave_shl:1 */, 0xf, 0xf, true);
 }
 // A value the wave holds in common, moved to scalar registers word by word
 // (e.g. a job descriptor read through a per-tile table), so that buffer

@@ -86,7 +86,6 @@ typedef unsigned short u2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ uint32_t pack_yx(int y, int x) { return ((uint32_t)y << 16) | (uint32_t)x; }
 __device__ __forceinline__ uint32_t umax32(uint32_t a, uint32_t b) { return a > b ? a : b; }
-__device__ __forceinline__ uint32_t umin32(uint32_t a, uint32_t b) { return a < b ? a : b; }
 
 // Coordinate arithmetic of the state words, in two forms.
 //
