@@ -15,8 +15,9 @@ The options of ``iwpp_options`` change only speed, never results:
 The tuner times a grid of candidates per (operation, connectivity, size
 bucket) on synthetic inputs of that bucket -- and, for the "batch" bucket, on
 a sample of the mixed 256-tile batch through ``run_batch`` -- checks that every
-candidate's output equals the default options' output byte for byte, keeps
-the fastest, and caches the choice as JSON keyed by device and library
+candidate's output equals the default options' output byte for byte, times the
+fastest and the default once more in turn, keeps it if it is faster every time
+(else the default), and caches the choice as JSON keyed by device and library
 version.  ``TunedContext`` applies the cached choice before each call,
 ``run_batch`` and ``batch_graph`` included.
 """
@@ -31,6 +32,8 @@ from . import Context, _lib
 
 DEFAULTS = {"persistent_blocks": 0, "mr_max_sweeps": 0, "mr_seed_sweeps": 0, "mr_list_capacity": 0, "wg_waves": 0,
             "stage_depth": 0, "mr_seed_strip": 0}
+
+TURNS = 6  # times the fastest candidate is timed in turn with the default, and has to beat it
 
 # Candidate grids.  0 means the library default (device-filling grid, the
 # workgroup size by operation and size -- four waves under a cap on the
@@ -147,31 +150,42 @@ def _job_outputs(jobs: list) -> list:
     return [t for j in jobs for t in ((j["out"],) if j["op"] in ("recon", "erode") else (j["sqdist"], j["nearest"]))]
 
 
+def _choose(ctx: Context, fn, outs: list, candidates: list, reps: int, what: str) -> tuple:
+    """(options, ms, default ms) for the calls `fn` makes, which write `outs`."""
+    import torch
+
+    def timed(opts, n):
+        ctx.set_options(**opts)
+        return _timed(fn, n)
+
+    saved = dict(ctx.options)
+    try:
+        timed(DEFAULTS, reps)
+        ref = [o.clone() for o in outs]
+        best, best_ms = None, float("inf")
+        for cand in candidates:
+            opts = dict(DEFAULTS, **cand)
+            ms = timed(opts, reps)
+            if not all(torch.equal(o, r) for o, r in zip(outs, ref)):
+                raise RuntimeError(f"tuning candidate {opts} changed {what}")
+            if ms < best_ms:
+                best, best_ms = opts, ms
+        # The smallest of many times is small by chance alone, and the default's
+        # own settings are among the candidates: the two in turn decide.
+        turns = [(timed(DEFAULTS, reps), timed(best, reps)) for _ in range(TURNS)]
+        default_ms, best_ms = min(d for d, _ in turns), min(b for _, b in turns)
+        if max(b for _, b in turns) < default_ms:
+            return best, best_ms, default_ms
+        return dict(DEFAULTS), default_ms, default_ms
+    finally:
+        ctx.set_options(**saved)
+
+
 def tune_jobs(ctx: Context, jobs: list, reps: int = 3) -> tuple:
     """Time every candidate of GRID["batch"] on ``ctx.run_batch(jobs)``.
     Returns (best options, best ms, default ms); raises if a candidate's
     outputs differ from the default options' outputs."""
-    import torch
-
-    saved = dict(ctx.options)
-    outs = _job_outputs(jobs)
-    fn = lambda: ctx.run_batch(jobs)
-    try:
-        ctx.set_options(**DEFAULTS)
-        default_ms = _timed(fn, reps)
-        ref = [o.clone() for o in outs]
-        best, best_ms = dict(DEFAULTS), default_ms
-        for cand in GRID["batch"]:
-            opts = dict(DEFAULTS, **cand)
-            ctx.set_options(**opts)
-            ms = _timed(fn, reps)
-            if not all(torch.equal(o, r) for o, r in zip(outs, ref)):
-                raise RuntimeError(f"tuning candidate {opts} changed a batch result")
-            if ms < best_ms:
-                best, best_ms = opts, ms
-        return best, best_ms, default_ms
-    finally:
-        ctx.set_options(**saved)
+    return _choose(ctx, lambda: ctx.run_batch(jobs), _job_outputs(jobs), GRID["batch"], reps, "a batch result")
 
 
 def _batch_sample(pixels: int, device) -> list:
@@ -209,7 +223,6 @@ def tune_bucket(ctx: Context, op: str, conn: int, key: str, reps: int = 3, seed:
     if op == "batch":
         return tune_jobs(ctx, _batch_sample(1 << int(key.rsplit("2^", 1)[1]) - 1, dev), reps)
     h, w = bucket_side(key)
-    saved = dict(ctx.options)
     x = _make_inputs(op, h, w, seed)
     if op == "recon":
         J, I = (torch.from_numpy(a).to(dev) for a in x)
@@ -222,22 +235,7 @@ def tune_bucket(ctx: Context, op: str, conn: int, key: str, reps: int = 3, seed:
         nr = torch.empty_like(sq)
         fn = lambda: ctx.edt(B, conn, out=(sq, nr))
         outs = [sq, nr]
-    try:
-        ctx.set_options(**DEFAULTS)
-        default_ms = _timed(fn, reps)
-        ref = [o.clone() for o in outs]
-        best, best_ms = dict(DEFAULTS), default_ms
-        for cand in GRID[op]:
-            opts = dict(DEFAULTS, **cand)
-            ctx.set_options(**opts)
-            ms = _timed(fn, reps)
-            if not all(torch.equal(o, r) for o, r in zip(outs, ref)):
-                raise RuntimeError(f"tuning candidate {opts} changed the result of {key}")
-            if ms < best_ms:
-                best, best_ms = opts, ms
-        return best, best_ms, default_ms
-    finally:
-        ctx.set_options(**saved)
+    return _choose(ctx, fn, outs, GRID[op], reps, f"the result of {key}")
 
 
 def autotune(buckets, device: int = 0, cache_path: str | None = None, reps: int = 3, force: bool = False) -> TuneCache:
