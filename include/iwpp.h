@@ -79,8 +79,9 @@ typedef struct {
    * 8-connectivity, 2 with 4-connectivity). */
   int32_t mr_seed_sweeps;
   /* Waves per workgroup of the persistent kernels, 4 or 8 (0 = automatic: 8
-   * for reconstructions and for distance transforms of at most 512 tiles of
-   * 48 x 48 in a launch, else 4; with persistent_blocks set, 4): the workgroup size (the paper's threads per
+   * for reconstructions and for distance transforms of at most two tiles of
+   * 48 x 48 per compute unit in a launch, 512 on an MI355X, else 4; with
+   * persistent_blocks set, 4): the workgroup size (the paper's threads per
    * block; a reconstruction tile is one wave's, a distance transform tile one
    * workgroup's). */
   int32_t wg_waves;

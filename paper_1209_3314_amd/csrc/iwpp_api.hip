@@ -337,7 +337,7 @@ int32_t launch_group(iwpp_ctx* ctx, const Group& g, uint8_t* scratch, uint8_t* f
     a.counts = reinterpret_cast<uint32_t*>(fixed + kOffCounts);
     a.ovf = reinterpret_cast<uint32_t*>(fixed + kOffOvf);
     a.stage_depth = (uint32_t)ctx->opt.stage_depth;
-    a.wg_waves = iwpp::edt_waves(ctx->opt.wg_waves, ctx->opt.persistent_blocks, g.ntiles);
+    a.wg_waves = (uint32_t)ctx->opt.wg_waves;
     a.bar = reinterpret_cast<iwpp::GridBarrier*>(fixed + kOffBarrier);
     a.stats = reinterpret_cast<unsigned long long*>(fixed + kOffStats);
     a.clock = reinterpret_cast<unsigned long long*>(fixed + kOffClock);

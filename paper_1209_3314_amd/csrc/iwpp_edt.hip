@@ -860,7 +860,12 @@ int edt_launch(const EdtArgs& a, int conn, int persistent_blocks, hipStream_t st
     *err = "EDT init launch failed";
     return -1;
   }
-  const int wpb = a.wg_waves == 8u ? 8 : 4;
+  int dev = 0, per_cu = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    *err = "device query failed";
+    return -1;
+  }
+  const int wpb = (int)edt_waves((int32_t)a.wg_waves, persistent_blocks, a.ntiles, cus);
   void* fn;
   if (wpb == 8)
     fn = conn == 8 ? (a.wide ? reinterpret_cast<void*>(&k_rounds<8, true, 8>) : reinterpret_cast<void*>(&k_rounds<8, false, 8>))
@@ -868,9 +873,7 @@ int edt_launch(const EdtArgs& a, int conn, int persistent_blocks, hipStream_t st
   else
     fn = conn == 8 ? (a.wide ? reinterpret_cast<void*>(&k_rounds<8, true, 4>) : reinterpret_cast<void*>(&k_rounds<8, false, 4>))
                    : (a.wide ? reinterpret_cast<void*>(&k_rounds<4, true, 4>) : reinterpret_cast<void*>(&k_rounds<4, false, 4>));
-  int dev = 0, per_cu = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64 * wpb, 0) != hipSuccess || per_cu < 1) {
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64 * wpb, 0) != hipSuccess || per_cu < 1) {
     *err = "occupancy query failed";
     return -1;
   }

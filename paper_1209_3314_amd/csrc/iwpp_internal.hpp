@@ -96,7 +96,7 @@ struct EdtArgs {
   uint32_t* counts;           // [3 round slots][8 shards][64] list fill levels (256 B apart; word 32: items taken)
   uint32_t* ovf;              // never set: a list holds each tile once
   uint32_t stage_depth;       // work-list items staged per wave before a flush (0 = the LDS maximum)
-  uint32_t wg_waves;          // waves per workgroup of the rounds kernel: 4 or 8
+  uint32_t wg_waves;          // waves per workgroup of the rounds kernel: 4, 8 or 0 = automatic (edt_waves)
   GridBarrier* bar;
   unsigned long long* stats;
   unsigned long long* clock;  // [kClockWords] round timeline (see kClockWords)
@@ -124,13 +124,17 @@ constexpr size_t kStatsBytes = 8 * 16 * 8;
 constexpr uint32_t recon_waves(int32_t wg_waves, int32_t persistent_blocks) {
   return wg_waves == 4 || (wg_waves == 0 && persistent_blocks > 0) ? 4u : 8u;
 }
-// Distance transform: a workgroup's waves share a tile.  Where every tile has a
-// workgroup of eight waves (two fit a CU) a visit is shorter with eight (us with
-// 4, 8: 99 tiles 290, 247; 441 tiles 295, 281; 529 tiles 317, 292); with more tiles
-// than that four workgroups of four hide more (625 tiles 380, 391; 4096^2 1064,
-// 1391).
-constexpr uint32_t edt_waves(int32_t wg_waves, int32_t persistent_blocks, uint64_t ntiles) {
-  return wg_waves == 8 || (wg_waves == 0 && persistent_blocks == 0 && ntiles <= 512) ? 8u : 4u;
+// Distance transform: a workgroup's waves share a tile.  `cus`: the device's compute
+// units, each of which holds two workgroups of eight waves.  Where every tile of the
+// launch has such a workgroup a visit is shorter with eight waves (30% features with
+// 8-connectivity, 15%, 30% with 4-connectivity; us with 4 and 8 waves: 400 tiles 382
+// 346, 648 560, 388 368; 512 tiles 342 319, 526 480, 358 346).  Past that some
+// workgroups visit two tiles a step; up to 20% more tiles eight waves still gain with
+// few features and lose with 4-connectivity (576 tiles 417 401, 632 569, 394 424; 600
+// tiles 417 426, 506 462, 414 441), and with many more tiles four workgroups of four
+// hide more (1024 tiles 402 467, 625 666, 423 523).
+constexpr uint32_t edt_waves(int32_t wg_waves, int32_t persistent_blocks, uint64_t ntiles, int cus) {
+  return wg_waves == 8 || (wg_waves == 0 && persistent_blocks == 0 && ntiles <= 2u * (uint64_t)cus) ? 8u : 4u;
 }
 
 // Optional per-launch event timing (iwpp_options.profile).  begin/end bracket

@@ -20,8 +20,9 @@ def waves(tmp_path_factory):
                     os.path.join(ROOT, "tests", "launch_rules.cpp"), "-o", str(exe), "-L/opt/rocm/lib", "-lamdhip64",
                     "-Wl,-rpath,/opt/rocm/lib"], check=True)
 
-    def run(wg_waves, blocks, tiles):
-        out = subprocess.run([str(exe), str(wg_waves), str(blocks), str(tiles)], check=True, capture_output=True, text=True)
+    def run(wg_waves, blocks, tiles, cus=256):
+        out = subprocess.run([str(exe)] + [str(v) for v in (wg_waves, blocks, tiles, cus)], check=True, capture_output=True,
+                             text=True)
         return tuple(int(v) for v in out.stdout.split())
 
     return run
@@ -37,7 +38,10 @@ def test_waves(waves, tiles):
 
 
 def test_automatic_edt_size_by_tiles(waves):
-    assert waves(0, 0, 1)[1] == 8 and waves(0, 0, 100000)[1] == 4
+    """Eight waves as long as every tile's workgroup is resident: two a compute unit."""
+    for cus in (32, 64, 256):
+        assert waves(0, 0, 1, cus)[1] == 8 and waves(0, 0, 2 * cus, cus)[1] == 8
+        assert waves(0, 0, 2 * cus + 1, cus)[1] == 4 and waves(0, 0, 100000, cus)[1] == 4
 
 
 def test_tuner_candidates_differ():
