@@ -17,7 +17,7 @@
 // feature is one at exactly that distance (ties: the smaller column, then the
 // upper row).
 //
-// Bound: 17 bytes a pixel move (mask 1, column rows 2 + 2, outputs 8, and the
+// Bound: 13 bytes a pixel move (mask 1, column rows 2 + 2, outputs 8, and the
 // segment masks), 43 us for 4096^2 at the copy rate.  Measured there (30%
 // features): k_mask 7 us, k_col 17 us, k_row 250 us, bound by the searches'
 // LDS round trips and integer arithmetic (one lane per row with a stack of

@@ -120,7 +120,8 @@ constexpr size_t kStatsBytes = 8 * 16 * 8;
 // Reconstruction, eight waves: twice as many take tiles from one workgroup's
 // share, and half as many workgroups meet at the barrier (us with 4, 8: 16384^2
 // 1456, 1374 and with 4-connectivity 1431, 1347; 4096^2 269, 258; 65536 x 65600
-// 12880, 12200; 1500 x 1301 154, 149; 512^2 114, 114; 20000 x 17000 2276, 2299).
+// 12880, 12200; 1500 x 1301 154, 149; 512^2 114, 114).  The 1% lost at 20000 x 17000
+// (1868, 1895) is its strips' (see `auto_strip`): seeded by single tiles it takes 1736.
 constexpr uint32_t recon_waves(int32_t wg_waves, int32_t persistent_blocks) {
   return wg_waves == 4 || (wg_waves == 0 && persistent_blocks > 0) ? 4u : 8u;
 }

@@ -1203,13 +1203,19 @@ __device__ __forceinline__ void visit_tile(WaveLds& L, WaveStage& s, uint32_t ro
   mark_reach(s, nx, tr, m, !stable, appended);
 }
 
-// Tiles per strip of the seed pass.  A strip for every wave has no slack: with
-// 8-connectivity it pays only where the waves' strips come out even, at least
-// 95% of the waves' steps being tiles (us, strips against single tiles in row
-// order: 16384^2 1457, 1476; 12000^2 811, 844; 32768^2 6733, 6994).  Otherwise
-// and with 4-connectivity single tiles, of which a workgroup's faster waves take
-// more (65536 x 65600, where 4100 strips meet 4096 waves: 14360, 12887; 6000^2
-// 342, 331; 16384^2 with 4 1497, 1441; 24000^2 3683, 3532; but 12000^2 828, 844).
+// Tiles per strip of the seed pass.  A strip carries the flood down a column of
+// tiles, but a strip for every wave has no slack, where of single tiles in row order
+// a workgroup's faster waves take more.  With 8-connectivity strips are taken where
+// they come out even, at least 95% of the waves' steps being tiles, as was measured
+// with four waves a workgroup (us, strips and single: 16384^2 1413, 1480; 12000^2
+// 922, 965; 32768^2 4888, 5039).  With eight, the default, they still gain up to 2%
+// where every wave has a whole strip (16384^2 1379, 1408; 12000^2 658, 680), but at
+// most other sizes single tiles are better, by up to 14% and the more the longer the
+// strips (20000 x 17000 1645, 1484; 32768^2 3721, 3487; 15189 x 16844 1710, 1593;
+// 8633 x 16884 1021, 1018): a line of its own for eight waves is open.  Where they
+// come out uneven (24000^2 2187, 2043; 65536 x 65600, where 4100 strips meet 4096
+// waves, 14360, 12887), and with 4-connectivity (16384^2 1188, 1158; 24000^2 2600,
+// 2409; 20000 x 17000 2020, 1837; 12000^2 794, 785), single tiles.
 __device__ __forceinline__ uint32_t auto_strip(const MrArgs& a, int conn, uint32_t nw) {
   const uint32_t S = (a.ntiles + nw - 1u) / nw;
   const uint32_t tx_n = (uint32_t)a.job0.tiles_x, ty_n = (uint32_t)a.job0.tiles_y;
