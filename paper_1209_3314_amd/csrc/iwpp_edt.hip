@@ -43,10 +43,10 @@
 // time goes to a visit's serial chain -- in cycles 5 k to load, per round 1.4 k
 // to list the sources and 0.8 k to push them, 5 k to store and list tiles --
 // which four workgroups per CU (40 KB of keys each) hide in part, and to the
-// slowest visit of each step.  Measured (30% features, whole call): 4096^2 1060
-// us, 389 x 517 247 us.  Before, a pull over the neighbourhood of every
-// change (26 x 26 tiles, four rounds a visit, one wave each; eleven
-// evaluations of nine candidates per changed pixel): 1430 and 530 us.
+// slowest visit of each step.  Measured (30% features, whole calls one after
+// another): 4096^2 1138 us, 389 x 517 246 us.  Before, a pull over the
+// neighbourhood of every change (26 x 26 tiles, four rounds a visit, one wave each;
+// eleven evaluations of nine candidates per changed pixel): 1515 and 516 us.
 //
 // The tiles of a step are a work list split into eight sub-lists, one per
 // group of workgroups (one per XCD), appended to with one atomic per flush; a

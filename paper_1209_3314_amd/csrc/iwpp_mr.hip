@@ -45,9 +45,10 @@
 // the time goes to the scans' dependence chains, which four waves per SIMD (9
 // KiB of LDS and 128 registers each) do not hide -- VALU issue is a little over
 // half -- and, with few tiles, to one visit and one barrier a round.  Measured
-// (16384^2 with 8- and 4-connectivity, 4096^2 and 512^2): 1370, 1350, 258, 114
-// us; before scans ran in pairs on lines in registers, with a barrier of seven
-// round trips and seed strips only: 1510, 1720, 345, 141.
+// (16384^2 with 8- and 4-connectivity, 4096^2 with 4, 512^2 with 8; whole calls one
+// after another): 1386, 1367, 252, 117 us; before scans ran in pairs on lines in
+// registers, with a barrier of seven round trips and seed strips only: 1520, 1725,
+// 324, 146.
 #include "iwpp_device.hpp"
 #include "iwpp_internal.hpp"
 

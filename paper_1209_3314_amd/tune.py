@@ -2,7 +2,8 @@
 
 The options of ``iwpp_options`` change only speed, never results:
   * ``wg_waves`` -- waves per workgroup of the persistent kernels (the
-    workgroup size; one wave holds one tile);
+    workgroup size; a reconstruction tile is one wave's, a distance transform
+    tile one workgroup's);
   * ``stage_depth`` -- work-list items a wave stages in LDS before one global
     atomic appends them (the depth of the paper's per-block queue);
   * ``mr_seed_strip`` -- tiles per vertical strip of the reconstruction seed
