@@ -282,10 +282,10 @@ int32_t iwpp_edt(iwpp_ctx* ctx, const uint8_t* binary, int32_t* sqdist, int32_t*
  * exact transform by the separable method of Meijster, Roerdink and
  * Hesselink (2000): per column the nearest feature in the column, then per
  * row the column x' that minimises (x - x')^2 + dy(x')^2, which never decreases
- * along the row, in integer arithmetic.  sqdist is the exact squared distance to the nearest feature;
- * nearest is y*width + x of a feature at exactly that distance (of several,
- * the one in the smallest column, then the smallest row).  No counters
- * (iwpp_get_stats reports zeros).  Scratch: 2.1 bytes per pixel.
+ * along the row, in integer arithmetic.  sqdist is the exact squared distance
+ * to the nearest feature; nearest is y*width + x of a feature at exactly that
+ * distance (of several, the one in the smallest column, then the smallest row).
+ * No counters (iwpp_get_stats reports zeros).  Scratch: 2.1 bytes per pixel.
  *   binary, sqdist, nearest, height, width : as iwpp_edt (no connectivity)
  * If the image has no feature, sqdist and nearest are -1 everywhere.
  * Errors: as iwpp_edt. */
